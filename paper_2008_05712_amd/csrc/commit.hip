@@ -318,6 +318,9 @@ __global__ void __launch_bounds__(kScanT) k_pair_offsets(const int2* __restrict_
     ca += part[0][k];
     cb += part[1][k];
   }
+  // (the offsets are 32-bit, so a tile's sums are carried modulo 2^32; the totals are not)
+  int64_t sa = 0, sb = 0;
+  const int64_t all_a = ca, all_b = cb;
   const int64_t last = min(first + span, n);
   for (int64_t base = first; base < last; base += kScanT) {
     const int64_t k = base + threadIdx.x;
@@ -331,12 +334,30 @@ __global__ void __launch_bounds__(kScanT) k_pair_offsets(const int2* __restrict_
     }
     ca += (uint32_t)ta;
     cb += (uint32_t)tb;
+    sa += x.x;
+    sb += x.y;
   }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-    if (a_end) a[n] = (int32_t)ca;
-    b[n] = (int32_t)cb;
-    tot[0] = ca;
-    tot[1] = cb;
+  if (blockIdx.x == gridDim.x - 1) {
+    sa = wave_sum64(sa);
+    sb = wave_sum64(sb);
+    __syncthreads();  // (part has been read)
+    if (lane == 0) {
+      part[0][w] = sa;
+      part[1][w] = sb;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      sa = all_a;
+      sb = all_b;
+      for (int k = 0; k < kScanT / 64; ++k) {
+        sa += part[0][k];
+        sb += part[1][k];
+      }
+      if (a_end) a[n] = (int32_t)sa;
+      b[n] = (int32_t)sb;
+      tot[0] = sa;
+      tot[1] = sb;
+    }
   }
 }
 

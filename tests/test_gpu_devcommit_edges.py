@@ -83,3 +83,26 @@ def test_union_of_overlapping_ranges(ctx, n):
     assert np.array_equal(got["pos"], pos)
     b.destroy()
     rig.close()
+
+
+@pytest.mark.parametrize("n_tasks,refused", [(511, False), (512, True), (1024, True), (1025, True)])
+def test_direct_entries_beyond_32_bits(ctx, n_tasks, refused):
+    # every task lists all 2^22 particles: 512 tasks hold 2^31 direct entries, and 1,024 (one tile of the
+    # offsets' scan) exactly 2^32, a total of zero in 32 bits
+    torch = torch_cuda()
+    n = 1 << 22
+    t = np.zeros(n_tasks, gc.TASK_DTYPE)
+    t["i_begin"] = np.arange(n_tasks, dtype=np.int32)
+    t["i_count"] = 1
+    t["j_nranges"] = 1
+    b = gc.Batch(ctx, gc.KIND_GRAV, n)
+    b.submit_device(torch.from_numpy(t.view(np.uint8).copy()).cuda(), torch.tensor([[0, n]], dtype=torch.int32).cuda(),
+                    torch.zeros(0, dtype=torch.int32).cuda(), 1)
+    print(f"[gpu] device commit of {n_tasks} tasks of 2^22 direct entries", flush=True)
+    if refused:
+        with pytest.raises(gc.GcError, match="2.31 entries") as e:
+            b.commit()
+        assert e.value.status == gc.GC_E_INVAL
+    else:
+        b.commit()
+    b.destroy()
