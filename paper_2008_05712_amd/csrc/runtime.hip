@@ -1100,16 +1100,19 @@ static gc_status build_adj_index(gc_batch b, int32_t n_nodes, hipStream_t s) {
                    (long long)x.bad_entry, n_nodes);
   if (r == kAdjIndexTooLarge) return set_err(c, GC_E_UNSUPPORTED, "gc_backward: more than 2^31 visits");
   if (r != kAdjIndexOk) return set_err(c, GC_E_NOMEM, "gc_backward: host memory for the gradient indices");
-  // records, then chunk sums, in one buffer; room for the quadrupole's, so one build serves both orders
-  b->adj_vdir = 3 * x.node_recs;
-  b->adj_part = b->adj_vdir + x.direct_recs;
-  hipError_t e = b->arec.ensure(sizeof(float4) * (size_t)(b->adj_part + 3 * (int64_t)std::max(x.chunks, 1)));
+  // records, then chunk sums, in one buffer; room for the quadrupole's, so one build serves both orders.  The buffers
+  // of an earlier build are overwritten or freed from here on, so its indices are void until this one is whole
+  b->adj_nodes = -1;
+  const int64_t vdir = 3 * x.node_recs, part = vdir + x.direct_recs;
+  hipError_t e = b->arec.ensure(sizeof(float4) * (size_t)(part + 3 * (int64_t)std::max(x.chunks, 1)));
   if (e == hipSuccess) e = b->aidx.ensure(x.bytes);
   if (e != hipSuccess) return set_err(c, GC_E_NOMEM, "gc_backward: gradient records");
   GC_HIP(c, hipMemcpyAsync(b->aidx.p, x.blob.get(), x.bytes, hipMemcpyHostToDevice, s));
   GC_HIP(c, hipStreamSynchronize(s));  // the host block goes out of scope
   b->adj = std::move(x);
   b->adj.blob.reset();
+  b->adj_vdir = vdir;
+  b->adj_part = part;
   b->adj_nodes = n_nodes;
   return GC_OK;
 }

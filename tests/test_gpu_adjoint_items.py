@@ -12,6 +12,7 @@ import pytest
 import oracle as O
 import paper_2008_05712_amd as gc
 import workloads as W
+from gpu_helpers import GravRig, whole
 from test_gpu_adjoint import close, grav_vjp_gpu
 
 pytestmark = pytest.mark.gpu
@@ -98,3 +99,53 @@ def test_lists_of_any_form(ctx, lists):
     if lists == "some_empty":
         w.j_nr = np.where(rng.random(w.n_tasks) < 0.5, w.j_nr, 0).astype(np.int32)
     _check(ctx, w, 2)
+
+
+def test_indices_after_a_failed_rebuild():
+    # A call with another n_nodes builds the indices again.  Where an allocation of that build fails, the call reports it
+    # and the next one, with the first n_nodes, builds its own; before, it would have taken the buffers for its own.
+    import torch
+    refuse = []
+
+    def alloc(nbytes, _user):
+        return None if refuse and refuse.pop() else torch.cuda.caching_allocator_alloc(int(nbytes), 0)
+
+    def free(ptr, _user):
+        torch.cuda.caching_allocator_delete(ptr)
+
+    c = gc.Context(0, allocator=(alloc, free))
+    w = W.build_grav(W.plummer(3000, 99), bucket=16, theta=0.8)
+    g = np.random.default_rng(100).normal(size=(w.n, 3)).astype(np.float32).astype(np.float64)
+    rig = GravRig(c, w)
+    b = rig.batch(whole(w))
+    rig.run(b, gc.REORG_PACK, order=2)
+    cot = torch.zeros((w.n, 4), dtype=torch.float32, device="cuda")
+    cot[:, :3] = torch.from_numpy(g.astype(np.float32)).cuda()
+    n = w.nodes.shape[0]
+    # the same nodes and 200,000 more that no list names: larger indices, so their buffer is allocated again
+    more = 200_000
+    nr = torch.from_numpy(np.concatenate([w.node_range, np.zeros((more, 2), np.int32)]).astype(np.int32)).cuda()
+    nodes = torch.cat([rig.nodes.reshape(n, -1), torch.zeros((more, rig.nodes.numel() // n), device="cuda")]).contiguous()
+    rp, rm = O.vjp_grav(w, g, order=2)
+
+    def backward(n_nodes):
+        gpos = torch.zeros((w.n, 4), dtype=torch.float32, device="cuda")
+        gmass = torch.zeros(w.n, dtype=torch.float32, device="cuda")
+        b.backward(gc.grav_params(order=2), nodes, nr, n_nodes, cot, gpos, gmass)
+        torch.cuda.synchronize()
+        for name, x, y in (("positions", gpos.cpu().numpy()[:, :3], rp), ("masses", gmass.cpu().numpy(), rm)):
+            ok, e = close(x, y)
+            assert ok, (n_nodes, name, e)
+
+    print("[gpu] adjoint indices, a refused allocation between two builds", flush=True)
+    backward(n)
+    refuse.append(True)
+    with pytest.raises(gc.GcError) as err:
+        backward(n + more)
+    assert err.value.status == gc.GC_E_NOMEM and not refuse
+    backward(n)
+    backward(n + more)
+    backward(n)
+    b.destroy()
+    rig.close()
+    c.close()
