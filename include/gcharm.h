@@ -547,6 +547,24 @@ gc_status gc_tree_walk_noalloc(gc_ctx ctx, int32_t n_nodes, const int32_t* node_
                                int32_t* r_first_dev, int32_t* node_idx_dev, int64_t node_cap, int32_t* ranges_dev,
                                int64_t range_cap, int64_t* totals, void* stream);
 
+/*
+ * The walk of gc_tree_walk (fixed_scratch 0) or gc_tree_walk_noalloc (1) into
+ * arrays of the lists' own size: between the count and the fill `room` is
+ * called, on the calling thread and with nothing of the walk in flight, with
+ * the totals; it sets the device addresses of the node entries (int32
+ * [n_entries]) and of the ranges (int32 [2 * n_ranges]) and returns 0.  It is
+ * not called when both lists are empty, and must not call this library.  Any
+ * other value, or a NULL array for a list that is not empty, ends the call with
+ * GC_E_NOMEM: totals and offsets are then set, no list is written.  Otherwise
+ * as gc_tree_walk, without GC_E_FULL; the lists are whole when it returns.
+ */
+typedef int32_t (*gc_walk_room)(int64_t n_entries, int64_t n_ranges, int32_t** node_idx_dev, int32_t** ranges_dev,
+                                void* user);
+gc_status gc_tree_walk_into(gc_ctx ctx, int32_t n_nodes, const int32_t* node_range_dev, const double* node_com_dev,
+                            const double* node_side_dev, const float* rec_dev, int32_t n_ids, int32_t n_buckets,
+                            const int32_t* bucket_node_dev, double theta, int32_t* n_first_dev, int32_t* r_first_dev,
+                            gc_walk_room room, void* user, int32_t fixed_scratch, int64_t* totals, void* stream);
+
 /* ---------------------------------------------------------------- graphs */
 
 /*

@@ -46,7 +46,7 @@ EXPORTED = ["gc_version", "gc_init", "gc_finalize", "gc_last_error", "gc_debug_i
             "gc_graph_capture", "gc_graph_launch", "gc_graph_destroy", "gc_autotune", "gc_occupancy", "gc_lj_count_pairs",
             "gc_launch_ewald", "gc_hybrid_create", "gc_hybrid_destroy", "gc_hybrid_record", "gc_hybrid_split",
             "gc_hybrid_state", "gc_lj_forces_cpu", "gc_combiner_create", "gc_combiner_destroy", "gc_combiner_arrive", "gc_combiner_poll", "gc_combiner_state",
-            "gc_tree_walk", "gc_tree_walk_noalloc"]
+            "gc_tree_walk", "gc_tree_walk_noalloc", "gc_tree_walk_into"]
 
 
 class EwaldParams(ctypes.Structure):
@@ -91,6 +91,8 @@ _lib = None
 VP, I32, I64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
 PI32 = ctypes.POINTER(ctypes.c_int32)
 PI64 = ctypes.POINTER(ctypes.c_int64)
+# Where a list walk's lists go: (n_entries, n_ranges, &node_idx, &ranges, user) -> 0, or anything else to give up.
+WALK_ROOM_FN = ctypes.CFUNCTYPE(I32, I64, I64, ctypes.POINTER(VP), ctypes.POINTER(VP), VP)
 
 
 def lib():
@@ -165,6 +167,8 @@ def lib():
                                PI64, VP]),
         "gc_tree_walk_noalloc": (I32, [VP, I32, VP, VP, VP, VP, I32, I32, VP, ctypes.c_double, VP, VP, VP, I64, VP,
                                        I64, PI64, VP]),
+        "gc_tree_walk_into": (I32, [VP, I32, VP, VP, VP, VP, I32, I32, VP, ctypes.c_double, VP, VP, WALK_ROOM_FN, VP, I32,
+                                    PI64, VP]),
     }
     for name, (res, args) in sig.items():
         f = getattr(L, name)
@@ -357,47 +361,50 @@ def lj_forces_cpu(tasks: np.ndarray, ranges: np.ndarray, rec: np.ndarray, eps_t,
 
 def tree_walk(ctx: "Context", node_range, node_com, node_side, rec, bucket_node, theta: float, stream=None,
               noalloc: bool = False):
-    """Barnes-Hut lists of every bucket on the device (gc_tree_walk, or gc_tree_walk_noalloc); device
-    tensors in, device tensors out: (n_first int32 [nb + 1], node_idx int32, r_first int32 [nb + 1],
+    """Barnes-Hut lists of every bucket on the device (gc_tree_walk_into, with or without the library's fixed
+    scratch); device tensors in, device tensors out: (n_first int32 [nb + 1], node_idx int32, r_first int32 [nb + 1],
     ranges int32 [., 2])."""
     import torch
-    fn = lib().gc_tree_walk_noalloc if noalloc else lib().gc_tree_walk
-    name = "gc_tree_walk_noalloc" if noalloc else "gc_tree_walk"
     dev = node_range.device
     nb = int(bucket_node.numel())
-    n_first = torch.empty(nb + 1, dtype=torch.int32, device=dev)
-    r_first = torch.empty(nb + 1, dtype=torch.int32, device=dev)
+    # The walk writes on `stream`, so the outputs come from that stream's memory: what the current one gave back may
+    # still be in use there.  They may be used on both.
+    handle, current = _stream(stream), torch.cuda.current_stream(dev)
+    on = current
+    if (handle or 0) != current.cuda_stream:
+        on = torch.cuda.ExternalStream(handle, device=dev) if handle else torch.cuda.default_stream(dev)
+
+    def empty(size):
+        if on is current:
+            return torch.empty(size, dtype=torch.int32, device=dev)
+        with torch.cuda.stream(on):
+            x = torch.empty(size, dtype=torch.int32, device=dev)
+        x.record_stream(current)
+        return x
+
+    n_first, r_first = empty(nb + 1), empty(nb + 1)
     totals = (ctypes.c_int64 * 2)()
-    args = (ctx.h, int(node_range.shape[0]), _ptr(node_range), _ptr(node_com), _ptr(node_side), _ptr(rec),
-            int(rec.shape[0]), nb, _ptr(bucket_node), float(theta), _ptr(n_first), _ptr(r_first))
-    # Room for the lists of buckets of some tens of particles at opening angles around 0.7 (300 to 800 node entries
-    # and 15 to 30 ranges), so that one walk serves; a call with too little room only counts, and the
-    # next one walks again.
-    room = [min(1024 * nb, 1 << 26), min(64 * nb, 1 << 23)]
-    while True:
+    lists, failed = [], []
+
+    def room(entries, n_ranges, idx_out, ranges_out, _user):
         try:
-            node_idx = torch.empty(max(room[0], 1), dtype=torch.int32, device=dev)
-            ranges = torch.empty((max(room[1], 1), 2), dtype=torch.int32, device=dev)
-        except torch.OutOfMemoryError:
-            if totals[0] or totals[1] or room == [0, 0]:  # the lists themselves do not fit
-                raise
-            room = [0, 0]
-            continue
-        st = fn(*args, _ptr(node_idx), room[0], _ptr(ranges), room[1], totals, _stream(stream))
-        if st != GC_E_FULL or (room[0] >= totals[0] and room[1] >= totals[1]):
-            break
-        node_idx = ranges = None
-        room = [int(totals[0]), int(totals[1])]  # sized by the call's counts
-    if st == GC_OK:  # (lists that would hold on to more than twice their room get their own, where there is any)
-        try:
-            if room[0] > 2 * totals[0]:
-                node_idx = node_idx[:totals[0]].clone()
-            if room[1] > 2 * totals[1]:
-                ranges = ranges[:totals[1]].clone()
-        except torch.OutOfMemoryError:
-            pass
-    ctx.check(st, name)
-    return n_first, node_idx[:totals[0]], r_first, ranges[:totals[1]]
+            lists.append(empty(max(entries, 1)))
+            lists.append(empty((max(n_ranges, 1), 2)))
+        except Exception as e:  # noqa: BLE001 - out of memory: raised to the caller below
+            failed.append(e)
+            return 1
+        idx_out[0], ranges_out[0] = lists[0].data_ptr(), lists[1].data_ptr()
+        return 0
+
+    st = lib().gc_tree_walk_into(ctx.h, int(node_range.shape[0]), _ptr(node_range), _ptr(node_com), _ptr(node_side),
+                                 _ptr(rec), int(rec.shape[0]), nb, _ptr(bucket_node), float(theta), _ptr(n_first),
+                                 _ptr(r_first), WALK_ROOM_FN(room), None, int(noalloc), totals, handle)
+    if failed:
+        raise failed[0]
+    ctx.check(st, "gc_tree_walk_noalloc" if noalloc else "gc_tree_walk")
+    if not lists:
+        lists = [empty(1), empty((1, 2))]
+    return n_first, lists[0][:totals[0]], r_first, lists[1][:totals[1]]
 
 
 def walk_tasks(ctx: "Context", b0: int, b1: int, bucket_node, node_range, n_first, r_first, stream=None):

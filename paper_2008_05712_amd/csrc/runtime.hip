@@ -2545,13 +2545,14 @@ struct ScopedBuf {  // device scratch of one call, freed on every return path
 // The walk proper, on scratch the caller provides: skip (int32 [n_nodes]), tot (5 int64: the two
 // totals, the invalid-bucket count, and the group walk's overflow count and order flag), and either the
 // group walk's buffers (grp) or optionally each bucket's room of the count pass (sn / sr, nullptr:
-// every bucket is walked twice).
+// every bucket is walked twice).  With `room` the lists go where it says once their totals are known, else into the
+// caller's arrays.
 static gc_status tree_walk_impl(gc_ctx c, int32_t n_nodes, const int32_t* node_range_dev,
                                 const double* node_com_dev, const double* node_side_dev, const float* rec_dev,
                                 int32_t n_ids, int32_t n_buckets, const int32_t* bucket_node_dev, double theta,
                                 int32_t* n_first_dev, int32_t* r_first_dev, int32_t* node_idx_dev, int64_t node_cap,
-                                int32_t* ranges_dev, int64_t range_cap, int64_t* totals, int32_t* skip,
-                                long long* dtot, int32_t* sn, int2* sr, GroupWalkArgs* grp, hipStream_t s) {
+                                int32_t* ranges_dev, int64_t range_cap, gc_walk_room room, void* user,
+                                int64_t* totals, int32_t* skip, long long* dtot, int32_t* sn, int2* sr, GroupWalkArgs* grp, hipStream_t s) {
   GC_HIP(c, launch_fill_i32(reinterpret_cast<int32_t*>(dtot), 0, 10, s));
   WalkArgs a{};
   a.range = reinterpret_cast<const int2*>(node_range_dev);
@@ -2590,7 +2591,11 @@ static gc_status tree_walk_impl(gc_ctx c, int32_t n_nodes, const int32_t* node_r
   if (h[2] != 0) return set_err(c, GC_E_INVAL, "gc_tree_walk: %lld buckets with a leaf index or id range out of bounds", h[2]);
   if (h[0] > INT32_MAX || h[1] > INT32_MAX)
     return set_err(c, GC_E_UNSUPPORTED, "gc_tree_walk: %lld node entries / %lld ranges exceed int32 offsets", h[0], h[1]);
-  if (h[0] > node_cap || h[1] > range_cap || (h[0] > 0 && !node_idx_dev) || (h[1] > 0 && !ranges_dev))
+  if (room) {
+    if (h[0] + h[1] > 0 && (room(h[0], h[1], &a.node_idx, &a.ranges, user) != 0 || (h[0] > 0 && !a.node_idx) ||
+                            (h[1] > 0 && !a.ranges)))
+      return set_err(c, GC_E_NOMEM, "gc_tree_walk_into: no room for %lld node entries and %lld ranges", h[0], h[1]);
+  } else if (h[0] > node_cap || h[1] > range_cap || (h[0] > 0 && !node_idx_dev) || (h[1] > 0 && !ranges_dev))
     return set_err(c, GC_E_FULL, "gc_tree_walk: need %lld node entries and %lld ranges (capacity %lld, %lld)", h[0],
                    h[1], (long long)node_cap, (long long)range_cap);
   if (grp) {
@@ -2633,11 +2638,12 @@ static gc_status tree_walk_args(gc_ctx c, int32_t n_nodes, const int32_t* node_r
   return GC_OK;
 }
 
-extern "C" gc_status gc_tree_walk(gc_ctx c, int32_t n_nodes, const int32_t* node_range_dev, const double* node_com_dev,
-                                  const double* node_side_dev, const float* rec_dev, int32_t n_ids, int32_t n_buckets,
-                                  const int32_t* bucket_node_dev, double theta, int32_t* n_first_dev,
-                                  int32_t* r_first_dev, int32_t* node_idx_dev, int64_t node_cap, int32_t* ranges_dev,
-                                  int64_t range_cap, int64_t* totals, void* stream) {
+// gc_tree_walk and gc_tree_walk_into (`room`: where the lists go).
+static gc_status tree_walk(gc_ctx c, int32_t n_nodes, const int32_t* node_range_dev, const double* node_com_dev,
+                           const double* node_side_dev, const float* rec_dev, int32_t n_ids, int32_t n_buckets,
+                           const int32_t* bucket_node_dev, double theta, int32_t* n_first_dev, int32_t* r_first_dev,
+                           int32_t* node_idx_dev, int64_t node_cap, int32_t* ranges_dev, int64_t range_cap,
+                           gc_walk_room room, void* user, int64_t* totals, void* stream) {
   if (!c) return GC_E_INVAL;
   GC_ENTER(c);
   hipStream_t s = S(stream);
@@ -2702,9 +2708,19 @@ extern "C" gc_status gc_tree_walk(gc_ctx c, int32_t n_nodes, const int32_t* node
   const bool rooms = kept && !group;
   return tree_walk_impl(c, n_nodes, node_range_dev, node_com_dev, node_side_dev, rec_dev, n_ids, n_buckets,
                         bucket_node_dev, theta, n_first_dev, r_first_dev, node_idx_dev, node_cap, ranges_dev,
-                        range_cap, totals, reinterpret_cast<int32_t*>(base + 256), reinterpret_cast<long long*>(base),
-                        rooms ? reinterpret_cast<int32_t*>(base + o_kn) : nullptr,
+                        range_cap, room, user, totals, reinterpret_cast<int32_t*>(base + 256),
+                        reinterpret_cast<long long*>(base), rooms ? reinterpret_cast<int32_t*>(base + o_kn) : nullptr,
                         rooms ? reinterpret_cast<int2*>(base + o_kr) : nullptr, kept && group ? &ga : nullptr, s);
+}
+
+extern "C" gc_status gc_tree_walk(gc_ctx c, int32_t n_nodes, const int32_t* node_range_dev, const double* node_com_dev,
+                                  const double* node_side_dev, const float* rec_dev, int32_t n_ids, int32_t n_buckets,
+                                  const int32_t* bucket_node_dev, double theta, int32_t* n_first_dev,
+                                  int32_t* r_first_dev, int32_t* node_idx_dev, int64_t node_cap, int32_t* ranges_dev,
+                                  int64_t range_cap, int64_t* totals, void* stream) {
+  return tree_walk(c, n_nodes, node_range_dev, node_com_dev, node_side_dev, rec_dev, n_ids, n_buckets, bucket_node_dev,
+                   theta, n_first_dev, r_first_dev, node_idx_dev, node_cap, ranges_dev, range_cap, nullptr, nullptr,
+                   totals, stream);
 }
 
 // ---------------------------------------------------------------- the walk without allocation
@@ -2737,12 +2753,11 @@ static hipError_t walk_scratch_address(void** out) {
   return hipSuccess;
 }
 
-extern "C" gc_status gc_tree_walk_noalloc(gc_ctx c, int32_t n_nodes, const int32_t* node_range_dev,
-                                          const double* node_com_dev, const double* node_side_dev,
-                                          const float* rec_dev, int32_t n_ids, int32_t n_buckets,
-                                          const int32_t* bucket_node_dev, double theta, int32_t* n_first_dev,
-                                          int32_t* r_first_dev, int32_t* node_idx_dev, int64_t node_cap,
-                                          int32_t* ranges_dev, int64_t range_cap, int64_t* totals, void* stream) {
+static gc_status tree_walk_noalloc(gc_ctx c, int32_t n_nodes, const int32_t* node_range_dev, const double* node_com_dev,
+                                   const double* node_side_dev, const float* rec_dev, int32_t n_ids, int32_t n_buckets,
+                                   const int32_t* bucket_node_dev, double theta, int32_t* n_first_dev,
+                                   int32_t* r_first_dev, int32_t* node_idx_dev, int64_t node_cap, int32_t* ranges_dev,
+                                   int64_t range_cap, gc_walk_room room, void* user, int64_t* totals, void* stream) {
   if (!c) return GC_E_INVAL;
   GC_ENTER(c);
   if (n_nodes > kWalkNoAllocMaxNodes)
@@ -2757,6 +2772,29 @@ extern "C" gc_status gc_tree_walk_noalloc(gc_ctx c, int32_t n_nodes, const int32
   unsigned char* base = static_cast<unsigned char*>(c->walk_scratch);
   return tree_walk_impl(c, n_nodes, node_range_dev, node_com_dev, node_side_dev, rec_dev, n_ids, n_buckets,
                         bucket_node_dev, theta, n_first_dev, r_first_dev, node_idx_dev, node_cap, ranges_dev,
-                        range_cap, totals, reinterpret_cast<int32_t*>(base + 256), reinterpret_cast<long long*>(base),
-                        nullptr, nullptr, nullptr, s);
+                        range_cap, room, user, totals, reinterpret_cast<int32_t*>(base + 256),
+                        reinterpret_cast<long long*>(base), nullptr, nullptr, nullptr, s);
+}
+
+extern "C" gc_status gc_tree_walk_noalloc(gc_ctx c, int32_t n_nodes, const int32_t* node_range_dev,
+                                          const double* node_com_dev, const double* node_side_dev,
+                                          const float* rec_dev, int32_t n_ids, int32_t n_buckets,
+                                          const int32_t* bucket_node_dev, double theta, int32_t* n_first_dev,
+                                          int32_t* r_first_dev, int32_t* node_idx_dev, int64_t node_cap,
+                                          int32_t* ranges_dev, int64_t range_cap, int64_t* totals, void* stream) {
+  return tree_walk_noalloc(c, n_nodes, node_range_dev, node_com_dev, node_side_dev, rec_dev, n_ids, n_buckets,
+                           bucket_node_dev, theta, n_first_dev, r_first_dev, node_idx_dev, node_cap, ranges_dev, range_cap,
+                           nullptr, nullptr, totals, stream);
+}
+
+extern "C" gc_status gc_tree_walk_into(gc_ctx c, int32_t n_nodes, const int32_t* node_range_dev,
+                                       const double* node_com_dev, const double* node_side_dev, const float* rec_dev,
+                                       int32_t n_ids, int32_t n_buckets, const int32_t* bucket_node_dev, double theta,
+                                       int32_t* n_first_dev, int32_t* r_first_dev, gc_walk_room room, void* user,
+                                       int32_t fixed_scratch, int64_t* totals, void* stream) {
+  if (!c) return GC_E_INVAL;
+  if (!room) return set_err(c, GC_E_INVAL, "gc_tree_walk_into: NULL room");
+  return (fixed_scratch ? tree_walk_noalloc : tree_walk)(c, n_nodes, node_range_dev, node_com_dev, node_side_dev, rec_dev,
+                                                         n_ids, n_buckets, bucket_node_dev, theta, n_first_dev,
+                                                         r_first_dev, nullptr, 0, nullptr, 0, room, user, totals, stream);
 }

@@ -1,5 +1,5 @@
-"""The list walk's one call: lists that fit the room it brings, lists far longer (counted, then walked again), and the
-storage that the returned lists hold on to."""
+"""The list walk's one call: lists of every length, in storage of their own size, whole on every stream when the call
+returns, and a call without memory for them."""
 import numpy as np
 import pytest
 
@@ -32,3 +32,58 @@ def test_lists_of_every_length(ctx, theta, noalloc):
         assert np.array_equal(a.cpu().numpy(), b)
     for x in (got[1], got[3]):  # at most twice what the lists need (or one entry)
         assert x.untyped_storage().nbytes() <= max(8 * x.numel(), 16)
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_lists_are_whole_on_the_callers_stream(ctx, noalloc):
+    # The walk runs on a stream of the caller's while the current one is busy; its lists are used on the caller's
+    # stream, and on a third one, with nothing to wait for.
+    import torch
+    w = W.build_grav(W.uniform_cube(20000, 98), bucket=16, theta=0.7)
+    leaf = np.ascontiguousarray(w.meta["leaf"], np.int32)
+    dev = [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in
+           (w.node_range.astype(np.int32), w.node_mom64[:, :3], w.node_side, w.rec, leaf)]
+    want = O.bh_walk(w.node_range, w.node_parent, w.node_side, w.node_mom64[:, :3], w.rec, leaf, w.theta)
+    own, third = torch.cuda.Stream(), torch.cuda.Stream()
+    busy = torch.ones((4096, 4096), device="cuda")
+    for x in (want[1], want[3]):  # (memory that they may get holds nothing like them)
+        torch.full(x.shape, -7, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    print("[gpu] walk on a stream of the caller's beside a busy one", flush=True)
+    for _ in range(40):
+        busy = busy @ busy * 1e-4
+    got = gc.tree_walk(ctx, *dev, w.theta, stream=own, noalloc=noalloc)
+    copies = []
+    for s in (own, third):
+        with torch.cuda.stream(s):
+            copies.append([x.clone() for x in got])
+        s.synchronize()
+    for c in copies:
+        for a, b in zip(c, want):
+            assert np.array_equal(a.cpu().numpy(), b)
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_lists_without_memory(ctx, noalloc, monkeypatch):
+    # No memory for a list: the error is torch's, and the next call walks as if nothing had been.
+    import torch
+    w = W.build_grav(W.uniform_cube(20000, 98), bucket=16, theta=0.7)
+    leaf = np.ascontiguousarray(w.meta["leaf"], np.int32)
+    dev = [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in
+           (w.node_range.astype(np.int32), w.node_mom64[:, :3], w.node_side, w.rec, leaf)]
+    want = O.bh_walk(w.node_range, w.node_parent, w.node_side, w.node_mom64[:, :3], w.rec, leaf, w.theta)
+    empty = torch.empty
+
+    def none(size, **kw):
+        if size in (want[1].size, tuple(want[3].shape)):
+            raise torch.OutOfMemoryError("lists")
+        return empty(size, **kw)
+
+    with monkeypatch.context() as m:
+        m.setattr(torch, "empty", none)
+        with pytest.raises(torch.OutOfMemoryError, match="lists"):
+            gc.tree_walk(ctx, *dev, w.theta, noalloc=noalloc)
+    got = gc.tree_walk(ctx, *dev, w.theta, noalloc=noalloc)
+    for a, b in zip(got, want):
+        assert np.array_equal(a.cpu().numpy(), b)
+        assert a.untyped_storage().nbytes() == 4 * a.numel()  # exactly the lists
