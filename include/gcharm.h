@@ -515,11 +515,14 @@ gc_status gc_backward(gc_batch batch, const gc_force_params* prm, const float* n
  * and totals are then set, the lists not written: call again with room);
  * GC_E_INVAL for a bucket whose leaf index or id range is out of bounds.  The
  * call waits on `stream` (twice: for the totals and at the end).  The context
- * keeps the walk's scratch until gc_finalize: with at least one bucket per
- * eight nodes (groups of 64 buckets are then walked together) about 10 KB per
- * bucket and 76 bytes per node of the largest call, otherwise room for up to
- * 2,048 node entries and 128 ranges per bucket (9 KB); buckets that do not fit
- * are walked twice.
+ * keeps the walk's scratch of the largest call until gc_finalize: 4 bytes per
+ * node, and, with at least one bucket per eight nodes (groups of 64 buckets are
+ * then walked together), 72 bytes per node and 44 + 120 p per bucket, p = 8 r + 1
+ * with r the least whole number for which 128 (2^r - 1) >= n_nodes (8 KB per
+ * bucket at 30,000 nodes, 13 KB at 10^6, 18 KB at 2^25).  With fewer buckets,
+ * more than 2^25 - 1 nodes or no memory for that, it is room for up to 2,048
+ * node entries and 128 ranges per bucket (9 KB); buckets that do not fit are
+ * walked twice, and where there is no memory for the room, all are.
  */
 gc_status gc_tree_walk(gc_ctx ctx, int32_t n_nodes, const int32_t* node_range_dev, const double* node_com_dev,
                        const double* node_side_dev, const float* rec_dev, int32_t n_ids, int32_t n_buckets,

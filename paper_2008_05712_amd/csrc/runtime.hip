@@ -2657,8 +2657,9 @@ static gc_status tree_walk(gc_ctx c, int32_t n_nodes, const int32_t* node_range_
   // The group walk needs buckets whose leaves lie close together in the numbering, or a group's lanes
   // open different nodes: it runs when there is at least one bucket per eight nodes (all the leaves of a
   // tree are most of its nodes).  A sparser list is walked one lane per bucket.
+  // Where the group walk's scratch does not fit, the other form's per-bucket room may (it is smaller from 65,409
+  // nodes on); where neither does, every bucket is walked twice, one lane each.
   DevBuf& keep = c->walk_keep;
-  const bool group = (int64_t)n_buckets * 8 >= n_nodes && n_nodes < (1 << 25);
   const size_t head = 256 + (size_t)pad_to((int64_t)sizeof(int32_t) * n_nodes, 256);
   size_t need = head;
   auto place = [&](size_t bytes) {
@@ -2666,12 +2667,18 @@ static gc_status tree_walk(gc_ctx c, int32_t n_nodes, const int32_t* node_range_
     need += (bytes + 255) / 256 * 256;
     return at;
   };
+  auto fits = [&](size_t bytes) {
+    if (keep.ensure(bytes) == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+  };
   GroupWalkArgs ga{};
   size_t o_node = 0, o_parent = 0, o_mark = 0, o_box = 0, o_perm = 0, o_over = 0, o_cnt = 0, o_pn = 0, o_sn = 0, o_sm = 0;
   size_t o_kn = 0, o_kr = 0;
+  bool group = (int64_t)n_buckets * 8 >= n_nodes && n_nodes <= kWalkGroupMaxNodes, rooms = false;
   if (group) {
     ga.n_groups = (n_buckets + kWalkGroup - 1) / kWalkGroup;
-    ga.n_parts = 2 * kWalkSplit * walk_rings(n_nodes) + 1;
+    ga.n_parts = walk_parts(n_nodes);
     const size_t parts = (size_t)ga.n_groups * ga.n_parts;
     o_node = place(sizeof(WalkNodeRec) * (size_t)n_nodes);
     o_parent = place(sizeof(int32_t) * (size_t)n_nodes);
@@ -2683,17 +2690,17 @@ static gc_status tree_walk(gc_ctx c, int32_t n_nodes, const int32_t* node_range_
     o_pn = place(sizeof(int32_t) * parts);
     o_sn = place(sizeof(int32_t) * parts * kWalkPartCap);
     o_sm = place(sizeof(ulonglong2) * parts * kWalkPartCap);
-  } else {
+    group = fits(need);
+  }
+  if (!group) {
+    need = head;
     o_kn = place(sizeof(int32_t) * kWalkCapNodes * (size_t)n_buckets);
     o_kr = place(sizeof(int2) * kWalkCapRanges * (size_t)n_buckets);
-  }
-  bool kept = keep.ensure(need) == hipSuccess;
-  if (!kept) {  // without the room every bucket is walked twice, one lane per bucket
-    (void)hipGetLastError();
-    if (keep.ensure(head) != hipSuccess) return set_err(c, GC_E_NOMEM, "gc_tree_walk: scratch");
+    rooms = fits(need);
+    if (!rooms && !fits(head)) return set_err(c, GC_E_NOMEM, "gc_tree_walk: scratch");
   }
   char* base = keep.as<char>();
-  if (kept && group) {
+  if (group) {
     ga.node = reinterpret_cast<WalkNodeRec*>(base + o_node);
     ga.parent = reinterpret_cast<int32_t*>(base + o_parent);
     ga.mark = reinterpret_cast<int32_t*>(base + o_mark);
@@ -2705,12 +2712,11 @@ static gc_status tree_walk(gc_ctx c, int32_t n_nodes, const int32_t* node_range_
     ga.step_node = reinterpret_cast<int32_t*>(base + o_sn);
     ga.step_mask = reinterpret_cast<ulonglong2*>(base + o_sm);
   }
-  const bool rooms = kept && !group;
   return tree_walk_impl(c, n_nodes, node_range_dev, node_com_dev, node_side_dev, rec_dev, n_ids, n_buckets,
                         bucket_node_dev, theta, n_first_dev, r_first_dev, node_idx_dev, node_cap, ranges_dev,
                         range_cap, room, user, totals, reinterpret_cast<int32_t*>(base + 256),
                         reinterpret_cast<long long*>(base), rooms ? reinterpret_cast<int32_t*>(base + o_kn) : nullptr,
-                        rooms ? reinterpret_cast<int2*>(base + o_kr) : nullptr, kept && group ? &ga : nullptr, s);
+                        rooms ? reinterpret_cast<int2*>(base + o_kr) : nullptr, group ? &ga : nullptr, s);
 }
 
 extern "C" gc_status gc_tree_walk(gc_ctx c, int32_t n_nodes, const int32_t* node_range_dev, const double* node_com_dev,

@@ -65,13 +65,17 @@ struct GroupWalkArgs {
   int32_t* part_n;            // per (group, interval): kept steps
   int32_t* step_node;         // kept steps: the node,
   ulonglong2* step_mask;      // the group's buckets that take it and those that list it as a leaf
-  int32_t n_groups, n_parts;  // n_parts = 2 * kWalkSplit * rings + 1
+  int32_t n_groups, n_parts;  // n_parts = walk_parts(n_nodes)
 };
-inline int walk_rings(int32_t n_nodes) {
+constexpr int walk_rings(int32_t n_nodes) {
   int r = 1;
   while (((int64_t)kWalkPart0 << r) - kWalkPart0 < n_nodes) ++r;
   return r;
 }
+constexpr int walk_parts(int32_t n_nodes) { return 2 * kWalkSplit * walk_rings(n_nodes) + 1; }
+constexpr int32_t kWalkGroupMaxNodes = (1 << 25) - 1;
+constexpr int kWalkMaxParts = 256;  // (the list fill takes an interval a thread)
+static_assert(walk_parts(kWalkGroupMaxNodes) == 153 && walk_parts(kWalkGroupMaxNodes) <= kWalkMaxParts, "intervals");
 
 hipError_t launch_group_walk(const WalkArgs& a, const GroupWalkArgs& g, hipStream_t s);
 // After the scan: every group's lists at their offsets, from the kept steps (groups marked `over` are

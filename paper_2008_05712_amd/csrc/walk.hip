@@ -380,7 +380,7 @@ typedef const __attribute__((address_space(4))) uint32_t* cst_words;
 __device__ __forceinline__ WalkNodeRec scalar_node(const WalkNodeRec* p, int k, int n) {
   WalkNodeRec r;
   constexpr int kWords = 11;  // com, s_take, begin, end, skip
-  // (a 32-bit byte offset: the group walk runs on fewer than 2^25 nodes)
+  // (a 32-bit byte offset: at most kWalkGroupMaxNodes nodes)
   typedef const __attribute__((address_space(4))) char* cst_bytes;
   cst_words q = (cst_words)((cst_bytes)(const void*)p + (uint32_t)(k < n ? k : n - 1) * 64u);
   uint32_t w[16];
@@ -518,10 +518,9 @@ __global__ void __launch_bounds__(256) k_group_walk(WalkArgs a, GroupWalkArgs g)
 // intervals' in order, flattened through the prefix of their counts) go through LDS kFillChunk at a
 // time, and each wavefront compacts the steps of its buckets, 64 at a time, by ballot onto their offsets.
 constexpr int kFillChunk = 512;
-constexpr int kMaxParts = 256;  // 2 kWalkSplit rings + 1 <= 145 for 2^25 nodes
 
 __global__ void __launch_bounds__(256) k_group_fill(WalkArgs a, GroupWalkArgs g) {
-  __shared__ int s_first[kMaxParts + 1];  // first flat step of each interval
+  __shared__ int s_first[kWalkMaxParts + 1];  // first flat step of each interval
   __shared__ int s_wave[4];
   __shared__ int2 s_range[kFillChunk];
   __shared__ int s_node[kFillChunk];

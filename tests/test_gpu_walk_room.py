@@ -87,3 +87,41 @@ def test_lists_without_memory(ctx, noalloc, monkeypatch):
     for a, b in zip(got, want):
         assert np.array_equal(a.cpu().numpy(), b)
         assert a.untyped_storage().nbytes() == 4 * a.numel()  # exactly the lists
+
+
+@pytest.mark.parametrize("refused", [0, 1, 2, 3])
+def test_scratch_that_does_not_fit(refused):
+    # The group walk's scratch, then the per-bucket rooms, then the subtree ends alone; no memory for those is an error.
+    import torch
+    w = W.build_grav(W.plummer(6000, 97), bucket=16, theta=0.7)
+    leaf = np.ascontiguousarray(w.meta["leaf"], np.int32)
+    asked = []
+
+    def alloc(nbytes, _user):
+        asked.append(int(nbytes))
+        return None if len(asked) <= refused else torch.cuda.caching_allocator_alloc(int(nbytes), 0)
+
+    def free(ptr, _user):
+        torch.cuda.caching_allocator_delete(ptr)
+
+    c = gc.Context(0, allocator=(alloc, free))
+    asked.clear()
+    dev = [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in
+           (w.node_range.astype(np.int32), w.node_mom64[:, :3], w.node_side, w.rec, leaf)]
+    n, nb = w.node_range.shape[0], leaf.size
+    rings = next(r for r in range(1, 32) if 128 * (2 ** r - 1) >= n)
+    head = 4 * n
+    sizes = [head + 72 * n + nb * (44 + 120 * (8 * rings + 1)), head + nb * (4 * 2048 + 8 * 128), head]
+    if refused == 3:
+        with pytest.raises(gc.GcError) as e:
+            gc.tree_walk(c, *dev, w.theta)
+        assert e.value.status == gc.GC_E_NOMEM
+    else:
+        got = gc.tree_walk(c, *dev, w.theta)
+        want = O.bh_walk(w.node_range, w.node_parent, w.node_side, w.node_mom64[:, :3], w.rec, leaf, w.theta)
+        for a, b in zip(got, want):
+            assert np.array_equal(a.cpu().numpy(), b)
+    assert len(asked) == min(refused + 1, 3)
+    for a, b in zip(asked, sizes):  # (the arrays are padded to 256 bytes, and the last group to 64 buckets)
+        assert b <= a <= b + 4096 + 64 * 20000, (asked, sizes)
+    c.close()
