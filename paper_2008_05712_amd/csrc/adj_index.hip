@@ -188,7 +188,8 @@ void group_tasks(const gc_task* tasks, int32_t ta, int32_t tb, int cap, int wave
   };
   for (int32_t t = ta; t < tb; ++t) {
     const int64_t n = count(t);
-    if (n == 0) {  // no visits, but a place among an item's consecutive tasks
+    if (n == 0) {  // no visits, but a place among an item's consecutive tasks (a closed item needs none)
+      if ((int)parts.size() >= max_tasks) close();
       if (!parts.empty()) parts.push_back(Part{t, 0, 0, 0, true});
       continue;
     }

@@ -149,3 +149,14 @@ def test_indices_after_a_failed_rebuild():
     b.destroy()
     rig.close()
     c.close()
+
+
+def test_a_long_run_of_tasks_without_sources(ctx):
+    # an item holds at most 16 tasks, those without nodes or direct ranges among them
+    w = W.build_grav(W.plummer(60000, 94), bucket=8, theta=1.0)
+    n = w.n_tasks
+    assert n > 16 * 256
+    bare = (np.arange(n) >= n // 8) & (np.arange(n) < n // 2)
+    w = _with_lists(w, [p[:0] if bare[t] else p for t, p in enumerate(_node_lists(w))])
+    w.j_nr = np.where(bare, 0, w.j_nr).astype(np.int32)
+    _check(ctx, w, 2, gc.REORG_PACK)
