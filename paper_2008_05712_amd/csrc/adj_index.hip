@@ -17,7 +17,6 @@
 #include <cstring>
 #include <new>
 #include <numeric>
-#include <system_error>
 #include <thread>
 
 #include "gc_internal.h"
@@ -224,7 +223,8 @@ void group_tasks(const gc_task* tasks, int32_t ta, int32_t tb, int cap, int wave
   close();
 }
 
-// f(0) ... f(n - 1) on up to `threads` threads; false if one of them ran out of memory.
+// f(0) ... f(n - 1) on up to `threads` threads; false if one of them ran out of memory.  (Nothing may be thrown from here
+// while threads run: std::bad_alloc comes from making one, too, beside std::system_error.)
 template <class F>
 bool run_jobs(int threads, int n, F&& f) {
   std::atomic<int> next{0};
@@ -232,7 +232,7 @@ bool run_jobs(int threads, int n, F&& f) {
   auto work = [&](int thread) {
     try {
       for (int j = next++; j < n; j = next++) f(thread, j);
-    } catch (const std::bad_alloc&) {
+    } catch (...) {
       ok = false;
     }
   };
@@ -240,7 +240,7 @@ bool run_jobs(int threads, int n, F&& f) {
   pool.reserve((size_t)std::max(threads - 1, 0));
   try {
     for (int t = 1; t < std::min(threads, n); ++t) pool.emplace_back(work, t);
-  } catch (const std::system_error&) {  // fewer threads than asked for
+  } catch (...) {  // fewer threads than asked for
   }
   work(0);
   for (std::thread& t : pool) t.join();

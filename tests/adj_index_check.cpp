@@ -1,14 +1,27 @@
 // Host checks of the gravity adjoint's indices (adj_index.hip is host code): random task sets, and for each the
 // properties that the kernels rely on.  Prints "ok" and returns 0, or names the first property that fails.
 #include <algorithm>
+#include <atomic>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
+#include <new>
 #include <random>
 #include <vector>
 
 #include "gc_internal.h"
 
 using namespace gc;
+
+// Allocations on any thread until one is refused (negative: none is).
+static std::atomic<long> g_left{-1};
+void* operator new(std::size_t n) {
+  if (g_left.load() >= 0 && g_left.fetch_sub(1) == 0) throw std::bad_alloc();
+  if (void* p = std::malloc(n ? n : 1)) return p;
+  throw std::bad_alloc();
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, std::size_t) noexcept { std::free(p); }
 
 namespace {
 
@@ -150,7 +163,32 @@ int check(const Input& x, const AdjIndex& a, bool direct, int form, int seed) {
 
 }  // namespace
 
-int main() {
+// A build in which the k-th allocation fails, for every k up to the last: std::bad_alloc or kAdjIndexNoMemory, and
+// nothing else (an exception that leaves with threads running would end the process).
+int without_memory() {
+  const Input x = make(2, 7, 900);  // (enough visits for several threads)
+  for (int n_cu : {1, 100000})
+    for (long k = 0;; ++k) {
+      AdjIndex a;
+      int r = kAdjIndexNoMemory;
+      g_left = k;
+      try {
+        r = adj_index_build(x.in(n_cu), &a);
+      } catch (const std::bad_alloc&) {
+      }
+      const bool refused = g_left.exchange(-1) < 0;
+      if (!refused) break;  // fewer than k + 1 allocations
+      if (r != kAdjIndexNoMemory && r != kAdjIndexOk) {  // (threads that could not be made are done without)
+        std::printf("allocation %ld: %d\n", k, r);
+        return 1;
+      }
+    }
+  std::puts("ok");
+  return 0;
+}
+
+int main(int argc, char** argv) {
+  if (argc > 1 && !std::strcmp(argv[1], "memory")) return without_memory();
   for (int form = 0; form < 3; ++form)
     for (int seed = 0; seed < 6; ++seed) {
       const Input x = make(form, seed, form == 2 ? 200 : 2000);

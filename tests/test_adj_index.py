@@ -25,3 +25,8 @@ def program(tmp_path_factory):
 def test_items_and_records(program):
     out = subprocess.run([program], capture_output=True, text=True, timeout=100)
     assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout + out.stderr
+
+
+def test_a_build_without_memory(program):
+    out = subprocess.run([program, "memory"], capture_output=True, text=True, timeout=100)
+    assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout + out.stderr
