@@ -262,8 +262,9 @@ __device__ __forceinline__ void adj_direct(const AdjSource<ORDER>& S, int rec0, 
     const float3 g = make_float3(T.gx[k], T.gy[k], T.gz[k]);
     const float dx = s.x - T.x[k], dy = s.y - T.y[k], dz = s.z - T.z[k];
     const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, __builtin_fmaf(dx, dx, eps2)));
-    const float ri = __builtin_amdgcn_rsqf(r2);
-    const float q = ri * ri, r3 = self == k ? 0.f : ri * q;  // j = i is skipped
+    // j = i is skipped (before any product: where eps^2 underflows, its 1 / r is infinite)
+    const float ri = self == k ? 0.f : __builtin_amdgcn_rsqf(r2);
+    const float q = ri * ri, r3 = ri * q;
     const float gd = __builtin_fmaf(g.z, dz, __builtin_fmaf(g.y, dy, g.x * dx));
     const float c1 = s.w * r3, c2 = -3.f * c1 * (gd * q);
     const float wx = __builtin_fmaf(c2, dx, c1 * g.x);

@@ -160,3 +160,31 @@ def test_a_long_run_of_tasks_without_sources(ctx):
     w = _with_lists(w, [p[:0] if bare[t] else p for t, p in enumerate(_node_lists(w))])
     w.j_nr = np.where(bare, 0, w.j_nr).astype(np.int32)
     _check(ctx, w, 2, gc.REORG_PACK)
+
+
+@pytest.mark.parametrize("mode", [gc.REORG_NONE, gc.REORG_PACK])
+def test_softening_whose_square_underflows(ctx, mode):
+    # soft_eps 1e-24: its square is zero in 32 bits, and the skipped pair of a particle with itself must stay skipped.
+    # Particles on a lattice, so that no other two lie close together; direct lists alone.
+    import torch
+    k = np.arange(8, dtype=np.float64)
+    xyz = np.stack(np.meshgrid(k, k, k, indexing="ij"), -1).reshape(-1, 3) + 0.25
+    rec = np.concatenate([xyz, np.full((512, 1), 1.0 / 512)], 1).astype(np.float32)
+    w = W.build_grav(rec, bucket=16, theta=0.0)
+    g = np.random.default_rng(101).normal(size=(w.n, 3)).astype(np.float32).astype(np.float64)
+    rig = GravRig(ctx, w)
+    b = rig.batch(whole(w))
+    b.reorganize(rig.pool, mode)
+    cot = torch.zeros((w.n, 4), dtype=torch.float32, device="cuda")
+    cot[:, :3] = torch.from_numpy(g.astype(np.float32)).cuda()
+    gpos = torch.zeros((w.n, 4), dtype=torch.float32, device="cuda")
+    gmass = torch.zeros(w.n, dtype=torch.float32, device="cuda")
+    nr = torch.from_numpy(np.ascontiguousarray(w.node_range)).cuda()
+    b.backward(gc.grav_params(order=1, eps=1e-24), rig.nodes, nr, w.nodes.shape[0], cot, gpos, gmass)
+    torch.cuda.synchronize()
+    rp, rm = O.vjp_grav(w, g, eps=1e-24, order=1)
+    for name, x, y in (("positions", gpos.cpu().numpy()[:, :3], rp), ("masses", gmass.cpu().numpy(), rm)):
+        ok, e = close(x, y)
+        assert ok, (name, e)
+    b.destroy()
+    rig.close()
