@@ -129,11 +129,12 @@ __device__ __forceinline__ int entry_at(const EntryGroup& g, int first, EntryTab
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)base));
 }
 
-// Squared distance of a point from a box.
+// Squared distance of a point from a box.  (A coordinate that is not a number counts as no distance, so such a source is
+// kept, and its pairs are evaluated: atoms that it is listed with become NaN rather than go on without it.)
 __device__ __forceinline__ float box_d2(float px, float py, float pz, float blx, float bly, float blz, float bhx,
                                         float bhy, float bhz) {
-  const float dx = px - __builtin_amdgcn_fmed3f(px, blx, bhx), dy = py - __builtin_amdgcn_fmed3f(py, bly, bhy),
-              dz = pz - __builtin_amdgcn_fmed3f(pz, blz, bhz);
+  const float dx = fmaxf(fmaxf(blx - px, px - bhx), 0.f), dy = fmaxf(fmaxf(bly - py, py - bhy), 0.f),
+              dz = fmaxf(fmaxf(blz - pz, pz - bhz), 0.f);
   return __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx));
 }
 
