@@ -878,8 +878,10 @@ __global__ void __launch_bounds__(256) k_lj_adj(LJAdjArgs A) {
 // five wavefronts a SIMD, 196 at seven).  284 us before the forward form's staging and this split.
 constexpr int kGRoom = 64;  // staged sources a wavefront has room for: one step's, a multiple of the slices
 
-// A staged source: its position, and 16 x its type | its entry << 8; its g / m.
-template <int NT, bool SHIFTED>
+// A staged source: its position, and 16 x its type | its entry << 8; its g / m.  A long sum over the sources would round at
+// its own size for each of a pair's two terms: a step's sources are summed on their own first, or (ONCE, where a wavefront
+// has one or two steps) a pair's terms before they are added.
+template <int NT, bool SHIFTED, bool ONCE>
 __device__ __forceinline__ void adj_gather_tile(const float4* __restrict__ p, const float4* __restrict__ hp,
                                                 const float4* __restrict__ to, int C, float tx, float ty, float tz,
                                                 float hx, float hy, float hz, const char* __restrict__ trow,
@@ -918,9 +920,15 @@ __device__ __forceinline__ void adj_gather_tile(const float4* __restrict__ p, co
     const float dhx = hx - hj.x, dhy = hy - hj.y, dhz = hz - hj.z;
     const float pp = __builtin_fmaf(dhz, ez, __builtin_fmaf(dhy, ey, dhx * ex));
     const float c2 = fp * pp;
-    acc[0] = __builtin_fmaf(f, dhx, __builtin_fmaf(c2, ex, acc[0]));
-    acc[1] = __builtin_fmaf(f, dhy, __builtin_fmaf(c2, ey, acc[1]));
-    acc[2] = __builtin_fmaf(f, dhz, __builtin_fmaf(c2, ez, acc[2]));
+    if (ONCE) {
+      acc[0] += __builtin_fmaf(f, dhx, c2 * ex);
+      acc[1] += __builtin_fmaf(f, dhy, c2 * ey);
+      acc[2] += __builtin_fmaf(f, dhz, c2 * ez);
+    } else {
+      acc[0] = __builtin_fmaf(f, dhx, __builtin_fmaf(c2, ex, acc[0]));
+      acc[1] = __builtin_fmaf(f, dhy, __builtin_fmaf(c2, ey, acc[1]));
+      acc[2] = __builtin_fmaf(f, dhz, __builtin_fmaf(c2, ez, acc[2]));
+    }
     acc[3] = __builtin_fmaf(f, ex, acc[3]);
     acc[4] = __builtin_fmaf(f, ey, acc[4]);
     acc[5] = __builtin_fmaf(f, ez, acc[5]);
@@ -1030,12 +1038,15 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) k
           wave_sync();
           if (active) {
             const char* row = reinterpret_cast<const char*>(trow);
+            float part[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
             if (G.shifted)
-              adj_gather_tile<NT, true>(src + sl * C, hsr + sl * C, T.to, C, tx, ty, tz, hx, hy, hz, row, p0, a.rc2, acc,
-                                        pa, pg_row);
+              adj_gather_tile<NT, true, SPLIT>(src + sl * C, hsr + sl * C, T.to, C, tx, ty, tz, hx, hy, hz, row, p0, a.rc2,
+                                               part, pa, pg_row);
             else
-              adj_gather_tile<NT, false>(src + sl * C, hsr + sl * C, T.to, C, tx, ty, tz, hx, hy, hz, row, p0, a.rc2, acc,
-                                         pa, pg_row);
+              adj_gather_tile<NT, false, SPLIT>(src + sl * C, hsr + sl * C, T.to, C, tx, ty, tz, hx, hy, hz, row, p0,
+                                                a.rc2, part, pa, pg_row);
+#pragma unroll
+            for (int q = 0; q < 6; ++q) acc[q] += part[q];
           }
           wave_sync();
         }
@@ -1050,9 +1061,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) k
         float sm[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         for (int x = 0; x < (SPLIT ? 4 : 1); ++x) {
           const float* part = SPLIT ? reinterpret_cast<const float*>(stage[x]) : red;
+          float of[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // (each wavefront's slices on their own)
           for (int sidx = 0; sidx < S; ++sidx)
 #pragma unroll
-            for (int q = 0; q < 6; ++q) sm[q] += part[q * 64 + sidx * icc + lane];
+            for (int q = 0; q < 6; ++q) of[q] += part[q * 64 + sidx * icc + lane];
+#pragma unroll
+          for (int q = 0; q < 6; ++q) sm[q] += of[q];
         }
         const int id = id0 + i0 + lane;
         const float4 g0 = dev::gld(A.gpos + id);

@@ -316,8 +316,13 @@ __global__ void __launch_bounds__(256) k_lj_gather(LJArgs a) {
           if (lane < S * C - held) src[held + lane] = make_float4(dev::kFar, dev::kFar, dev::kFar, 0.f);
           wave_sync();
           if (active) {
-            if (G.shifted) gather_tile<true, ONE>(src + sl * C, T.to, C, tx, ty, tz, trow, p0.y, a.rc2, Fx, Fy, Fz);
-            else gather_tile<false, ONE>(src + sl * C, T.to, C, tx, ty, tz, trow, p0.y, a.rc2, Fx, Fy, Fz);
+            // (summed on their own first: neighbouring sources pull alike, and one long sum of them rounds worse)
+            float gx = 0.f, gy = 0.f, gz = 0.f;
+            if (G.shifted) gather_tile<true, ONE>(src + sl * C, T.to, C, tx, ty, tz, trow, p0.y, a.rc2, gx, gy, gz);
+            else gather_tile<false, ONE>(src + sl * C, T.to, C, tx, ty, tz, trow, p0.y, a.rc2, gx, gy, gz);
+            Fx += gx;
+            Fy += gy;
+            Fz += gz;
           }
           wave_sync();
           held = 0;
@@ -359,11 +364,15 @@ __global__ void __launch_bounds__(256) k_lj_gather(LJArgs a) {
         float sx = 0.f, sy = 0.f, sz = 0.f;
         for (int q = 0; q < (SPLIT ? 4 : 1); ++q) {
           const float* f = SPLIT ? reinterpret_cast<const float*>(stage[q]) : fr;
+          float wx = 0.f, wy = 0.f, wz = 0.f;
           for (int s = 0; s < S; ++s) {
-            sx += f[s * icc + lane];
-            sy += f[64 + s * icc + lane];
-            sz += f[128 + s * icc + lane];
+            wx += f[s * icc + lane];
+            wy += f[64 + s * icc + lane];
+            wz += f[128 + s * icc + lane];
           }
+          sx += wx;
+          sy += wy;
+          sz += wz;
         }
         if (ONE) {
           sx *= p0.x; sy *= p0.x; sz *= p0.x;

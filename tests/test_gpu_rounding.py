@@ -1,0 +1,60 @@
+"""Errors against 64 bits at rounding level: the relative L2 error of whole outputs, root mean square over some seeds,
+against that of the kernels that summed every pair term or every visit apart (measured with the same inputs; one part in
+200 is allowed for the order of the sums)."""
+import numpy as np
+import pytest
+
+import oracle as O
+import paper_2008_05712_amd as gc
+import workloads as W
+from test_gpu_adjoint import _lj_vjp_gpu
+from test_gpu_lj import LJRig
+
+pytestmark = pytest.mark.gpu
+
+TYPES = {1: ([1.0], [1.0], [1.0]), 2: ([1.0, 0.5], [1.0, 0.88], [1.0, 1.0])}
+
+
+def _atoms(side, types, seed):
+    xyz, _v, L = W.fcc_modulated(side, side, side, 0.8442, int(3.6 * side ** 3), seed=seed)
+    t = np.random.default_rng(seed + 1).integers(0, types, xyz.shape[0])
+    return W.build_lj(xyz, t, L, 2.5, *TYPES[types])
+
+
+def _rel(a, b):
+    return float(np.linalg.norm(np.asarray(a, np.float64) - b) / np.linalg.norm(b))
+
+
+def lj(ctx, side, types, seed):
+    w = _atoms(side, types, seed)
+    rig = LJRig(ctx, w)
+    acc = rig.run(gc.REORG_NONE)[:, :3]
+    rig.close()
+    return _rel(acc, O.lj_tasks(w))
+
+
+def lj_gradient(ctx, side, types, seed):
+    w = _atoms(side, types, seed)
+    g = np.random.default_rng(seed + 2).normal(size=(w.n, 3)).astype(np.float32).astype(np.float64)
+    return _rel(_lj_vjp_gpu(ctx, w, g)[0][0], O.vjp_lj(w, g)[0])
+
+
+BEFORE = [
+    (lj, 28, 1, 4.1579e-7), (lj, 28, 2, 4.4243e-7), (lj, 12, 1, 4.1364e-7),
+    (lj_gradient, 28, 1, 4.2296e-7), (lj_gradient, 28, 2, 4.3595e-7), (lj_gradient, 12, 1, 4.2743e-7),
+    (lj_gradient, 12, 2, 4.5830e-7),
+]
+
+
+def error(ctx, f, a, b):
+    seeds = 20 if a == 12 else 3  # (the smallest box: the sums of a few close pairs)
+    return float(np.sqrt(np.mean([f(ctx, a, b, 700 + 10 * s) ** 2 for s in range(seeds)])))
+
+
+@pytest.mark.parametrize("f,a,b,before", BEFORE)
+def test_no_further_from_64_bits(f, a, b, before):
+    ctx = gc.Context(0)
+    e = error(ctx, f, a, b)
+    print(f"[gpu] {f.__name__} {a} {b}: {e:.4g} (before {before:.4g})", flush=True)
+    ctx.close()
+    assert e <= 1.005 * before
