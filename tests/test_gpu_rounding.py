@@ -7,6 +7,7 @@ import pytest
 import oracle as O
 import paper_2008_05712_amd as gc
 import workloads as W
+from gpu_helpers import GravRig, whole
 from test_gpu_adjoint import _lj_vjp_gpu
 from test_gpu_lj import LJRig
 
@@ -39,10 +40,30 @@ def lj_gradient(ctx, side, types, seed):
     return _rel(_lj_vjp_gpu(ctx, w, g)[0][0], O.vjp_lj(w, g)[0])
 
 
+def ewald(ctx, n, quad, seed):
+    w = W.build_grav(W.uniform_cube(n, seed), bucket=32, theta=0.7)
+    rng = np.random.default_rng(seed + 2)
+    com = rng.uniform(0.4, 0.6, 3).astype(np.float32)
+    S = (np.array([0.083, 0.083, 0.083, 0.0, 0.0, 0.0]) + rng.normal(size=6) * 1e-3).astype(np.float32) if quad else None
+    ids = np.sort(rng.choice(n, 20000, replace=False))
+    rig = GravRig(ctx, w)
+    b = rig.batch(whole(w))
+    b.reorganize(rig.pool, gc.REORG_NONE)
+    rig.acc.zero_()
+    b.ewald(gc.ewald_params(1.0, 1.0, com, S=S), rig.acc)
+    rig.torch.cuda.synchronize()
+    acc = rig.acc.cpu().numpy()[ids, :3]
+    b.destroy()
+    rig.close()
+    return _rel(acc, O.ewald(w.rec[ids, :3], 1.0, 1.0, 1.0, com.astype(np.float64), 2.0, 1, 10,
+                             S=None if S is None else S.astype(np.float64)))
+
+
 BEFORE = [
     (lj, 28, 1, 4.1579e-7), (lj, 28, 2, 4.4243e-7), (lj, 12, 1, 4.1364e-7),
     (lj_gradient, 28, 1, 4.2296e-7), (lj_gradient, 28, 2, 4.3595e-7), (lj_gradient, 12, 1, 4.2743e-7),
     (lj_gradient, 12, 2, 4.5830e-7),
+    (ewald, 40000, True, 3.2664e-7), (ewald, 80000, True, 3.2824e-7), (ewald, 80000, False, 2.5482e-7),
 ]
 
 
