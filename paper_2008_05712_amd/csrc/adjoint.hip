@@ -287,7 +287,10 @@ struct AdjCursor {
 };
 
 // One item per workgroup of W wavefronts.  The table holds NV floats per
-// distinct source, one array per value, then the sources' indices.  A chunk's records are loaded while
+// distinct source, one array per value, for a direct source what its dL/dm lost in rounding, then the sources'
+// indices.  (The mass gradients are the largest by far, and a source near 16 tasks is added to some 50 times: without that
+// value their error against 64 bits was 1.58e-7 of 80,000 Plummer particles, 1.53e-7 when every visit had
+// its own sum; now 1.50e-7, for 3 us of 1,100 at 262,144.)  A chunk's records are loaded while
 // the one before is computed, and their places while the one before that is.
 template <bool PACKED, int ORDER, bool NODES>
 __device__ __forceinline__ void adj_item(const GravAdjArgs& A, const AdjItem& it, float* table) {
@@ -297,10 +300,11 @@ __device__ __forceinline__ void adj_item(const GravAdjArgs& A, const AdjItem& it
   const int wid = uniform(threadIdx.x >> 6);
   const int t0 = uniform(it.t0), nt = uniform(it.nt), cap = uniform(it.count), base = uniform(it.base);
   const float G = A.f.G, eps2 = A.f.eps2;
-  int* src = reinterpret_cast<int*>(table + NV * cap);
+  float* low = table + NV * cap;  // (direct)
+  int* src = reinterpret_cast<int*>(table + (NODES ? NV : NV + 1) * cap);
   {
     const int32_t* from = NODES ? A.nsrc : PACKED ? A.dsrc_packed : A.dsrc_id;
-    for (int k = threadIdx.x; k < NV * cap; k += 64 * W) table[k] = 0.f;
+    for (int k = threadIdx.x; k < (NODES ? NV : NV + 1) * cap; k += 64 * W) table[k] = 0.f;
     for (int k = threadIdx.x; k < cap; k += 64 * W) src[k] = gld(from + base + k);
   }
   __syncthreads();
@@ -380,7 +384,14 @@ __device__ __forceinline__ void adj_item(const GravAdjArgs& A, const AdjItem& it
       else adj_direct<ORDER>(here, rec0, T, tb, eps2, acc);
       if (here.slot >= 0) {
 #pragma unroll
-        for (int q = 0; q < NV; ++q) table[q * cap + here.slot] += acc[q];
+        for (int q = 0; q < NV; ++q) {
+          const float t = table[q * cap + here.slot], sum = t + acc[q];
+          table[q * cap + here.slot] = sum;
+          if (!NODES && q == 3) {
+            const float b = sum - t;
+            low[here.slot] += (t - (sum - b)) + (acc[q] - b);
+          }
+        }
       }
       more = n1.k == cur.k && n1.b0 == cur.b0;
       cur = n1;
@@ -397,6 +408,8 @@ __device__ __forceinline__ void adj_item(const GravAdjArgs& A, const AdjItem& it
 #pragma unroll
     for (int q = 0; q < NV; ++q) v[q] = G * table[q * cap + u];
     if (!NODES) {
+      const float rest = low[u];
+      if (rest == rest) v[3] = G * (table[3 * cap + u] + rest);  // (an infinite sum leaves no rest)
       gst(A.vdir + base + u, make_float4(v[0], v[1], v[2], v[3]));
     } else {
       float4* q = A.vnode + (int64_t)(ORDER == 2 ? 3 : 1) * (base + u);
@@ -1097,7 +1110,7 @@ namespace {
 template <bool PACKED, int ORDER, bool NODES>
 hipError_t adj_items(const GravAdjArgs& a, int n_items, int most, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
-  const size_t lds = 4 * ((NODES && ORDER == 2 ? 10 : 4) + 1) * (size_t)most;
+  const size_t lds = 4 * (NODES && ORDER == 2 ? 11 : NODES ? 5 : 6) * (size_t)most;
   if (lds > (NODES ? kAdjNodeBytes : kAdjDirectBytes)) return hipErrorInvalidValue;
   hipLaunchKernelGGL((k_grav_adj<PACKED, ORDER, NODES>), dim3(n_items),
                      dim3(64 * (NODES ? kAdjNodeWaves : kAdjDirectWaves)), lds, s, a);
@@ -1105,7 +1118,7 @@ hipError_t adj_items(const GravAdjArgs& a, int n_items, int most, hipStream_t s)
 }
 template <bool PACKED, int ORDER>
 hipError_t adj_both(const GravAdjArgs& a, int n_cu, hipStream_t s) {
-  const size_t nodes = 4 * ((ORDER == 2 ? 10 : 4) + 1) * (size_t)a.max_nodes, direct = 4 * 5 * (size_t)a.max_direct;
+  const size_t nodes = 4 * (ORDER == 2 ? 11 : 5) * (size_t)a.max_nodes, direct = 4 * 6 * (size_t)a.max_direct;
   const size_t lds = nodes > direct ? nodes : direct;
   if (lds > kAdjNodeBytes) return hipErrorInvalidValue;
   const int by_lds = (int)(163840 / (lds + 1)), by_regs = ORDER == 2 ? 4 : 6;  // workgroups per CU

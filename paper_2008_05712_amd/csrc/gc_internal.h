@@ -308,16 +308,17 @@ struct GravAdjArgs {
                            // yz and two unused floats (3 float4 per record)
   float4* vdir;            // per direct record: dL/dx (3) and dL/dm of the source
 };
-// The LDS table of one item (10 floats and an index per quadrupole node, 4 and an index per direct source):
+// The LDS table of one item (10 floats and an index per quadrupole node, 5 and an index per direct source):
 // its room, and so the most distinct sources of an item; wavefronts per item.
 // Three node items of four wavefronts fit a CU, and nine direct items of two.  Measured on Plummer 262,144
 // (quadrupole; task kernel + record sums): nodes 613 + 44 us with 51,200 bytes and 16 tasks, 591 + 144
 // with 40,960 bytes (less than one task's neighbourhood: more records), 616 + 65 with 8 tasks, 705 + 44
-// with three wavefronts, 878 + 34 with five and 24 tasks; direct 172 + 34 us with 16,384 bytes, 192 + 28
-// with 20,480, 151 + 50 with 12,288 and 8 tasks, 201 + 34 with one wavefront.
+// with three wavefronts, 878 + 34 with five and 24 tasks; direct (20 bytes a source) 172 + 34 us with 16,384 bytes, 192 + 28
+// with 20,480, 151 + 50 with 12,288 and 8 tasks, 201 + 34 with one wavefront.  With 24 bytes a source (20 before: 1,093 to
+// 1,103 us the whole step, 21 ms its first) 16,384 bytes: 1,095 us, but 23.5 ms the first; 17,664: 1,106 us; 19,456: 1,111.
 constexpr size_t kAdjNodeBytes = 51200;
-constexpr size_t kAdjDirectBytes = 16384;
-constexpr int kAdjMaxNodes = (int)(kAdjNodeBytes / 44), kAdjMaxDirect = (int)(kAdjDirectBytes / 20);
+constexpr size_t kAdjDirectBytes = 17664;
+constexpr int kAdjMaxNodes = (int)(kAdjNodeBytes / 44), kAdjMaxDirect = (int)(kAdjDirectBytes / 24);
 constexpr int kAdjNodeWaves = 4, kAdjDirectWaves = 2;
 constexpr int kAdjMaxTasks = 16;  // tasks per item
 // Records of one node are summed in chunks of at most this many (one wavefront per chunk), so that a

@@ -8,7 +8,7 @@ import oracle as O
 import paper_2008_05712_amd as gc
 import workloads as W
 from gpu_helpers import GravRig, whole
-from test_gpu_adjoint import _lj_vjp_gpu
+from test_gpu_adjoint import _lj_vjp_gpu, grav_vjp_gpu
 from test_gpu_lj import LJRig
 
 pytestmark = pytest.mark.gpu
@@ -40,6 +40,13 @@ def lj_gradient(ctx, side, types, seed):
     return _rel(_lj_vjp_gpu(ctx, w, g)[0][0], O.vjp_lj(w, g)[0])
 
 
+def gravity_gradient(ctx, plummer, order, seed):
+    w = W.build_grav(W.plummer(80000, seed) if plummer else W.uniform_cube(80000, seed), bucket=16, theta=0.7)
+    g = np.random.default_rng(seed + 2).normal(size=(w.n, 3)).astype(np.float32).astype(np.float64)
+    got, want = grav_vjp_gpu(ctx, w, g, order=order), O.vjp_grav(w, g, order=order)
+    return _rel(got[1], want[1])  # (of the masses: larger than the positions' by far)
+
+
 def ewald(ctx, n, quad, seed):
     w = W.build_grav(W.uniform_cube(n, seed), bucket=32, theta=0.7)
     rng = np.random.default_rng(seed + 2)
@@ -63,6 +70,7 @@ BEFORE = [
     (lj, 28, 1, 4.1579e-7), (lj, 28, 2, 4.4243e-7), (lj, 12, 1, 4.1364e-7),
     (lj_gradient, 28, 1, 4.2296e-7), (lj_gradient, 28, 2, 4.3595e-7), (lj_gradient, 12, 1, 4.2743e-7),
     (lj_gradient, 12, 2, 4.5830e-7),
+    (gravity_gradient, True, 2, 1.5339e-7), (gravity_gradient, False, 1, 1.4928e-7),
     (ewald, 40000, True, 3.2664e-7), (ewald, 80000, True, 3.2824e-7), (ewald, 80000, False, 2.5482e-7),
 ]
 
