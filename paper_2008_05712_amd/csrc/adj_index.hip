@@ -6,9 +6,10 @@
 // kVisitChunk) and by source id, by counting sorts that keep the record order.
 //
 // The tasks are cut into segments that threads index side by side (an item never spans two), and
-// everything the device needs goes up in one block: one allocation and one copy.  For Plummer 262,144
+// what the device cannot write itself goes up in one block: one allocation and one copy.  For Plummer 262,144
 // (18.4 M node and 9.3 M direct visits) that and the two passes over the visits are what a first call
-// waits for.
+// waits for.  Batches of few tasks have an item a task: the sorts alone are made here (4,096 uniform particles
+// 0.41 ms the first call, 0.55 with records, places and cuts written here; 8,000: 1.2 and 1.6).
 #include <sys/mman.h>
 
 #include <algorithm>
@@ -247,21 +248,21 @@ bool run_jobs(int threads, int n, F&& f) {
   return ok;
 }
 
-// Records grouped by key: start (n_keys + 1 entries) and, in record order within a key, rec.  A thread counts and places
-// a slice of the records; the slices' places of a key follow one another.
-bool sort_by_key(int threads, const int32_t* key, size_t n, int32_t n_keys, std::vector<int32_t>* start, int32_t* rec) {
-  const int P = (int)std::max<size_t>(1, std::min<size_t>((size_t)threads, n / 50000));
+// Records grouped by key: start (n_keys + 1 entries) and, in record order within a key, rec.  each(p, f) calls f(record,
+// key) for slice p of the records, in order.  A thread counts and places a slice; the slices' places of a key follow
+// one another.
+template <class Each>
+bool sort_by_key(int threads, int P, size_t n, int32_t n_keys, Each&& each, std::vector<int32_t>* start, int32_t* rec) {
   const size_t K = (size_t)n_keys;
   std::vector<int32_t> fill((size_t)P * K, 0), base((size_t)P, 0);
   start->resize(K + 1);
-  auto slice = [&](int p) { return n * (size_t)p / (size_t)P; };
   auto keys = [&](int p) { return K * (size_t)p / (size_t)P; };
-  bool ok = run_jobs(P, P, [&](int, int p) {
-    int32_t* f = fill.data() + (size_t)p * K;
-    for (size_t r = slice(p), e = slice(p + 1); r < e; ++r) ++f[(size_t)key[r]];
+  bool ok = run_jobs(threads, P, [&](int, int p) {
+    int32_t* const f = fill.data() + (size_t)p * K;
+    each(p, [f](int32_t, int32_t k) { ++f[(size_t)k]; });
   });
   // the first place of each slice of each key: within a run of keys, then past the runs before
-  ok = ok && run_jobs(P, P, [&](int, int q) {
+  ok = ok && run_jobs(threads, P, [&](int, int q) {
     int32_t at = 0;
     for (size_t k = keys(q); k < keys(q + 1); ++k)
       for (int p = 0; p < P; ++p) {
@@ -278,22 +279,20 @@ bool sort_by_key(int threads, const int32_t* key, size_t n, int32_t n_keys, std:
     b = sum;
     sum += c;
   }
-  ok = ok && run_jobs(P, P, [&](int, int q) {
+  ok = ok && run_jobs(threads, P, [&](int, int q) {
     for (size_t k = keys(q); k < keys(q + 1); ++k) {
       for (int p = 0; p < P; ++p) fill[(size_t)p * K + k] += base[(size_t)q];
       (*start)[k] = fill[k];
     }
   });
   (*start)[K] = (int32_t)n;
-  return ok && run_jobs(P, P, [&](int, int p) {
-    int32_t* f = fill.data() + (size_t)p * K;
-    for (size_t r = slice(p), e = slice(p + 1); r < e; ++r) rec[(size_t)f[(size_t)key[r]]++] = (int32_t)r;
+  return ok && run_jobs(threads, P, [&](int, int p) {
+    int32_t* const f = fill.data() + (size_t)p * K;
+    each(p, [f, rec](int32_t r, int32_t k) { rec[(size_t)f[(size_t)k]++] = r; });
   });
 }
 
-}  // namespace
-
-namespace {
+int slices(int threads, size_t n) { return (int)std::max<size_t>(1, std::min<size_t>((size_t)threads, n / 50000)); }
 
 // One kind of source, ready to be laid out.
 struct Side {
@@ -302,46 +301,55 @@ struct Side {
   int64_t visits = 0;
 };
 
-// Items longest first: a long one that starts last would leave most of the chip idle (814 -> 613 us for the
-// node items of Plummer 262,144).
+// Items longest first, to a part in 1,024 of the longest: a long one that starts last would leave most of the chip idle
+// (814 -> 613 us for the node items of Plummer 262,144).
 void longest_first(std::vector<AdjItem>* items, const std::vector<int64_t>& work) {
-  std::vector<int32_t> order(items->size());
-  std::iota(order.begin(), order.end(), 0);
-  std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return work[(size_t)x] > work[(size_t)y]; });
-  std::vector<AdjItem> sorted;
-  sorted.reserve(items->size());
-  for (int32_t k : order) sorted.push_back((*items)[(size_t)k]);
+  constexpr int kSteps = 1024;
+  const int64_t most = work.empty() ? 1 : std::max<int64_t>(1, *std::max_element(work.begin(), work.end()));
+  auto step = [&](size_t k) { return kSteps - 1 - (int)((double)work[k] / (double)most * (kSteps - 1)); };
+  std::vector<int32_t> at(kSteps + 1, 0);
+  for (size_t k = 0; k < work.size(); ++k) ++at[(size_t)step(k) + 1];
+  std::partial_sum(at.begin(), at.end(), at.begin());
+  std::vector<AdjItem> sorted(items->size());
+  for (size_t k = 0; k < work.size(); ++k) sorted[(size_t)at[(size_t)step(k)]++] = (*items)[k];
   items->swap(sorted);
 }
 
-// The places of the arrays, and room for them.
-bool lay_out(const AdjIndexInput& in, const Side& node, const Side& direct, AdjIndex* out) {
+// The places of the arrays, and room for those that are built here.
+bool lay_out(const AdjIndexInput& in, const Side& node, const Side& direct, bool one_task, AdjIndex* out) {
   size_t bytes = 0;
   auto place = [&](int which, size_t b) {
     out->at[which] = bytes;
     bytes += (b + 255) / 256 * 256 + 256;
   };
+  auto places = [&]() {
+    place(AdjIndex::kNodePlace, 2 * (size_t)node.visits);
+    place(AdjIndex::kDirectPlace, 2 * (size_t)direct.visits);
+    place(AdjIndex::kNodeCuts, 4 * node.cuts);
+    place(AdjIndex::kDirectCuts, 4 * direct.cuts);
+    place(AdjIndex::kNodeKey, 4 * node.recs);
+    place(AdjIndex::kDirectKey, 4 * direct.recs);
+  };
   place(AdjIndex::kNodeItems, sizeof(AdjItem) * node.items.size());
   place(AdjIndex::kDirectItems, sizeof(AdjItem) * direct.items.size());
   place(AdjIndex::kNodeFirst, 4 * ((size_t)in.n_tasks + 1));
-  place(AdjIndex::kNodePlace, 2 * (size_t)node.visits);
-  place(AdjIndex::kDirectPlace, 2 * (size_t)direct.visits);
-  place(AdjIndex::kNodeCuts, 4 * node.cuts);
-  place(AdjIndex::kDirectCuts, 4 * direct.cuts);
-  place(AdjIndex::kNodeKey, 4 * node.recs);
-  place(AdjIndex::kDirectKey, 4 * direct.recs);
-  place(AdjIndex::kDirectPacked, 4 * direct.recs);
   place(AdjIndex::kNodeSorted, 4 * node.recs);
   place(AdjIndex::kDirectSorted, 4 * direct.recs);
-  place(AdjIndex::kDirectSortedKey, 4 * direct.recs);
+  if (!one_task) places();
   place(AdjIndex::kChunkFirst, 4 * ((size_t)in.n_nodes + 1));
   // at most one partial chunk per node beside the full ones
   place(AdjIndex::kChunks, 8 * (node.recs / kVisitChunk + (size_t)in.n_nodes + 1));
+  const size_t here = bytes;
+  if (one_task) places();
+  place(AdjIndex::kDirectPacked, 4 * direct.recs);
+  place(AdjIndex::kDirectSortedKey, 4 * direct.recs);
+  out->room = bytes;
+  out->one_task = one_task;
   // (huge pages where the system gives them: the first touch of small ones takes as long as filling them)
   const size_t huge = (size_t)2 << 20;
-  out->blob.reset(static_cast<char*>(std::aligned_alloc(huge, (bytes + huge - 1) / huge * huge)));
+  out->blob.reset(static_cast<char*>(std::aligned_alloc(huge, (here + huge - 1) / huge * huge)));
   if (!out->blob) return false;
-  if (bytes >= huge) (void)madvise(out->blob.get(), bytes, MADV_HUGEPAGE);
+  if (here >= huge) (void)madvise(out->blob.get(), here, MADV_HUGEPAGE);
   auto put = [&](int which, const std::vector<AdjItem>& v) {
     if (!v.empty()) std::memcpy(out->blob.get() + out->at[which], v.data(), sizeof(AdjItem) * v.size());
   };
@@ -361,11 +369,11 @@ T* array_of(AdjIndex* x, int which) {
   return reinterpret_cast<T*>(x->blob.get() + x->at[which]);
 }
 
-// The records of each node in chunks.
-bool sort_nodes(const AdjIndexInput& in, int threads, AdjIndex* out) {
+// The records of each node in chunks; each: as in sort_by_key.
+template <class Each>
+bool sort_nodes(const AdjIndexInput& in, int threads, int P, Each&& each, AdjIndex* out) {
   std::vector<int32_t> start;
-  if (!sort_by_key(threads, array_of(out, AdjIndex::kNodeKey), (size_t)out->node_recs, in.n_nodes, &start,
-                   array_of(out, AdjIndex::kNodeSorted)))
+  if (!sort_by_key(threads, P, (size_t)out->node_recs, in.n_nodes, each, &start, array_of(out, AdjIndex::kNodeSorted)))
     return false;
   int32_t* first = array_of(out, AdjIndex::kChunkFirst);
   int32_t* chunk = array_of(out, AdjIndex::kChunks);
@@ -385,34 +393,21 @@ bool sort_nodes(const AdjIndexInput& in, int threads, AdjIndex* out) {
   return true;
 }
 
-// The direct records by source id, and each one's position in the packed records.
-bool sort_direct(const AdjIndexInput& in, int threads, AdjIndex* out) {
-  const int32_t* key = array_of(out, AdjIndex::kDirectKey);
-  int32_t* rec = array_of(out, AdjIndex::kDirectSorted);
-  const size_t n = (size_t)out->direct_recs;
+// The direct records by source id.
+template <class Each>
+bool sort_direct(const AdjIndexInput& in, int threads, int P, Each&& each, AdjIndex* out) {
   std::vector<int32_t> start;
-  if (!sort_by_key(threads, key, n, in.n_ids, &start, rec)) return false;
-  std::vector<int32_t>& pos = start;  // (no longer needed)
-  for (int32_t u = 0; u < in.n_union; ++u) pos[(size_t)in.U[u]] = u;
-  int32_t* packed = array_of(out, AdjIndex::kDirectPacked);
-  int32_t* sorted = array_of(out, AdjIndex::kDirectSortedKey);
-  const int jobs = 1 + (int)std::min<size_t>(n / 50000, 63);
-  return run_jobs(threads, jobs, [&](int, int j) {
-    for (size_t r = n * (size_t)j / (size_t)jobs, e = n * (size_t)(j + 1) / (size_t)jobs; r < e; ++r) {
-      packed[r] = pos[(size_t)key[r]];
-      sorted[r] = key[rec[r]];
-    }
-  });
+  return sort_by_key(threads, P, (size_t)out->direct_recs, in.n_ids, each, &start, array_of(out, AdjIndex::kDirectSorted));
 }
 
-// Both, side by side where there is more than one thread: a first call of 30,000 uniform particles in buckets of 16
-// takes 3.6 instead of 3.9 ms, 57,555 in buckets of 32 4.4 instead of 4.65, 60,000 Plummer 7.5 instead of 8.6; below
-// that line a second thread costs more than it saves (8,000 uniform: 1.77 against 1.53).
-bool sort_both(const AdjIndexInput& in, int threads, AdjIndex* out) {
+// f(0, threads) and f(1, threads), side by side where there is more than one thread (60,000 Plummer particles in buckets
+// of 32: 7.5 instead of 8.6 ms the first call).
+template <class F>
+bool both_sides(int threads, F&& f) {
   const int at_once = std::min(threads, 2), half = threads / at_once;
   std::atomic<bool> ok{true};
   const bool room = run_jobs(at_once, 2, [&](int, int j) {
-    if (!(j ? sort_nodes(in, half, out) : sort_direct(in, half, out))) ok = false;
+    if (!f(j, half)) ok = false;
   });
   return room && ok;
 }
@@ -443,11 +438,11 @@ std::vector<int32_t> cut_tasks(int segs, const std::vector<int32_t>& noff, const
   return cut;
 }
 
-// An item per task (or stretch of a long one) and a record per visit, in order: straight into place.
+// An item per task (or stretch of a long one) and a record per visit, in order: records, places and cuts follow from the
+// items alone and are written on the device; only the sorts are made here, from the lists themselves.
 int index_tasks(const AdjIndexInput& in, int threads, const std::vector<int32_t>& noff, const std::vector<int32_t>& joff,
                 AdjIndex* out) {
   Side side[2];
-  std::vector<AdjItem> items[2];  // in task order
   const std::vector<int32_t>* off[2] = {&noff, &joff};
   const int cap[2] = {kAdjMaxNodes, kAdjMaxDirect}, waves[2] = {kAdjNodeWaves, kAdjDirectWaves};
   for (int k = 0; k < 2; ++k) {
@@ -456,55 +451,50 @@ int index_tasks(const AdjIndexInput& in, int threads, const std::vector<int32_t>
     for (int32_t t = 0; t < in.n_tasks; ++t)
       for (int32_t e = o[(size_t)t]; e < o[(size_t)t + 1]; e += cap[k]) {
         const int32_t n = std::min(cap[k], o[(size_t)t + 1] - e);
-        items[k].push_back(AdjItem{t, 1, e, n, (int32_t)side[k].cuts});
+        side[k].items.push_back(AdjItem{t, 1, e, n, (int32_t)side[k].cuts});
         side[k].cuts += (size_t)waves[k] + 1;
         work.push_back((int64_t)(in.tasks[t].i_count + 1) * n);
       }
     side[k].recs = (size_t)o[(size_t)in.n_tasks];
     side[k].visits = o[(size_t)in.n_tasks];
-    side[k].items = items[k];
     longest_first(&side[k].items, work);
   }
-  if (!lay_out(in, side[0], side[1], out)) return kAdjIndexNoMemory;
+  if (!lay_out(in, side[0], side[1], true, out)) return kAdjIndexNoMemory;
   std::memcpy(array_of(out, AdjIndex::kNodeFirst), noff.data(), 4 * noff.size());
   const int segs = threads == 1 ? 1 : 4 * threads;
   const std::vector<int32_t> cut = cut_tasks(segs, noff, joff);
   std::atomic<int64_t> bad{-1};
   bool ok = run_jobs(threads, segs, [&](int, int g) {
-    const int32_t ta = cut[(size_t)g], tb = cut[(size_t)g + 1];
-    const int64_t wrong = bad_node(in, ta, tb);
-    if (wrong >= 0) {
-      bad = wrong;
-      return;
-    }
-    int32_t* key = array_of(out, AdjIndex::kNodeKey);
-    int32_t* id = array_of(out, AdjIndex::kDirectKey);
-    for (int32_t t = ta; t < tb; ++t) {
-      const gc_task& tk = in.tasks[t];
-      std::copy(in.nodes + tk.n_first, in.nodes + tk.n_first + tk.n_count, key + noff[(size_t)t]);
-      int32_t* to = id + joff[(size_t)t];
-      for (int32_t r = 0; r < tk.j_nranges; ++r) {
-        const int32_t g0 = in.ranges[2 * (tk.j_first + r)], gn = in.ranges[2 * (tk.j_first + r) + 1];
-        std::iota(to, to + gn, g0);
-        to += gn;
-      }
-    }
-    for (int k = 0; k < 2; ++k) {
-      int32_t* cuts = array_of(out, k ? AdjIndex::kDirectCuts : AdjIndex::kNodeCuts);
-      uint16_t* place = array_of<uint16_t>(out, k ? AdjIndex::kDirectPlace : AdjIndex::kNodePlace);
-      auto it = std::lower_bound(items[k].begin(), items[k].end(), ta, [](const AdjItem& i, int32_t t) { return i.t0 < t; });
-      for (; it != items[k].end() && it->t0 < tb; ++it) {
-        const int32_t e0 = it->base - (*off[k])[(size_t)it->t0];
-        for (int x = 0; x <= waves[k]; ++x) cuts[it->cuts + x] = e0 + (int32_t)((int64_t)it->count * x / waves[k]);
-        std::iota(place + it->base, place + it->base + it->count, (uint16_t)0);
-      }
-    }
+    const int64_t wrong = bad_node(in, cut[(size_t)g], cut[(size_t)g + 1]);
+    if (wrong >= 0) bad = wrong;
   });
   if (bad >= 0) {
     out->bad_entry = bad;
     return kAdjIndexBadNode;
   }
-  ok = ok && sort_both(in, threads, out);
+  ok = ok && both_sides(threads, [&](int k, int n) {
+    const std::vector<int32_t>& o = *off[k];
+    const int P = slices(n, side[k].recs);
+    // the tasks of slice p
+    auto first = [&](int p) {
+      if (p == P) return in.n_tasks;
+      return (int32_t)(std::lower_bound(o.begin(), o.end() - 1, (int32_t)(side[k].recs * (size_t)p / (size_t)P)) - o.begin());
+    };
+    if (k)
+      return sort_direct(in, n, P, [&](int p, auto&& f) {
+        int32_t r = o[(size_t)first(p)];
+        for (int32_t t = first(p), e = first(p + 1); t < e; ++t)
+          for (int32_t j = in.tasks[t].j_first, je = j + in.tasks[t].j_nranges; j < je; ++j)
+            for (int32_t g = in.ranges[2 * j], ge = g + in.ranges[2 * j + 1]; g < ge; ++g) f(r++, g);
+      }, out);
+    return sort_nodes(in, n, P, [&](int p, auto&& f) {
+      for (int32_t t = first(p), e = first(p + 1); t < e; ++t) {
+        const int32_t* nodes = in.nodes + in.tasks[t].n_first;
+        const int32_t r = o[(size_t)t];
+        for (int32_t v = 0, c = in.tasks[t].n_count; v < c; ++v) f(r + v, nodes[v]);
+      }
+    }, out);
+  });
   return ok ? kAdjIndexOk : kAdjIndexNoMemory;
 }
 
@@ -523,18 +513,22 @@ int adj_index_build(const AdjIndexInput& in, AdjIndex* out) {
   }
   noff[(size_t)T] = (int32_t)nv;
   joff[(size_t)T] = (int32_t)nd;
-  // enough items to fill the chip (four per CU), then as many tasks in each as share well; below four tasks
-  // per item the shared records save less than finding them costs
+  // Enough items to fill the chip (four per CU), then as many tasks in each as share well.  Below five tasks an item the
+  // shared records save less than finding them costs: uniform 57,555 in buckets of 32 (4,096 tasks) 2.6 ms the first
+  // call and 145 us the others with an item a task, 4.2 and 162 with items of four; 30,000 in buckets of 16 1.9 and
+  // 93 against 3.4 and 91.  Plummer 60,000 in buckets of 32 (6,455 tasks, items of six): 5.0 and 317 against 7.7 and 278,
+  // 40,000 in buckets of 16 (seven) 5.9 and 282 against 6.2 and 203.
   const int per_item = T / (4 * std::max(in.n_cu, 1));
   const int64_t visits = nv + nd;
   const int32_t most_keys = std::max(in.n_nodes, in.n_ids);
-  // one thread up to 600,000 visits (starting the others would cost more: 1.5 against 1.8 ms for 8,000 uniform
-  // particles in buckets of 16), then one per 200,000, at most 16, and at most 512 MB of marks among them
+  // one thread up to 600,000 visits (starting the others would cost more: with every visit's record written here 1.5
+  // against 1.8 ms for 8,000 uniform particles in buckets of 16), then one per 200,000, at most 16, and at most 512 MB of
+  // marks among them
   const int threads =
       visits < 600000 ? 1
                       : (int)std::min<int64_t>({16, std::max(1u, std::thread::hardware_concurrency()), 1 + visits / 200000,
                                                 std::max<int64_t>(1, (512ll << 20) / (int64_t)(sizeof(Mark) * (size_t)most_keys + 1))});
-  if (per_item < 4) return index_tasks(in, threads, noff, joff, out);
+  if (per_item < 5) return index_tasks(in, threads, noff, joff, out);
   const int max_tasks = std::min(kAdjMaxTasks, per_item);
   const int segs = threads == 1 ? 1 : 4 * threads;
   const std::vector<int32_t> cut = cut_tasks(segs, noff, joff);
@@ -604,7 +598,7 @@ int adj_index_build(const AdjIndexInput& in, AdjIndex* out) {
     side[k].visits = k ? nd : nv;
     longest_first(&side[k].items, work);
   }
-  if (!lay_out(in, side[0], side[1], out)) return kAdjIndexNoMemory;
+  if (!lay_out(in, side[0], side[1], false, out)) return kAdjIndexNoMemory;
   std::memcpy(array_of(out, AdjIndex::kNodeFirst), noff.data(), 4 * noff.size());
   ok = run_jobs(threads, 2 * segs, [&](int, int job) {
     const int k = job & 1;
@@ -617,7 +611,15 @@ int adj_index_build(const AdjIndexInput& in, AdjIndex* out) {
     put(k ? AdjIndex::kDirectCuts : AdjIndex::kNodeCuts, q.cuts, cut0[k][g]);
     put(k ? AdjIndex::kDirectKey : AdjIndex::kNodeKey, q.key, rec0[k][g]);
   });
-  ok = ok && sort_both(in, threads, out);
+  ok = ok && both_sides(threads, [&](int k, int n) {
+    const int32_t* key = array_of(out, k ? AdjIndex::kDirectKey : AdjIndex::kNodeKey);
+    const size_t recs = side[k].recs;
+    const int P = slices(n, recs);
+    auto each = [&](int p, auto&& f) {
+      for (size_t r = recs * (size_t)p / (size_t)P, e = recs * (size_t)(p + 1) / (size_t)P; r < e; ++r) f((int32_t)r, key[r]);
+    };
+    return k ? sort_direct(in, n, P, each, out) : sort_nodes(in, n, P, each, out);
+  });
   return ok ? kAdjIndexOk : kAdjIndexNoMemory;
 }
 

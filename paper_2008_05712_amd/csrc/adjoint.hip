@@ -630,6 +630,46 @@ __global__ void __launch_bounds__(256) k_record_sums(SumArgs a, int32_t direct_b
   }
 }
 
+// What the indices hold of an item that is one task, or a stretch of one: its visits are its records, in order, and the
+// wavefronts' cuts are even.  One wavefront an item, node items first.
+__global__ void __launch_bounds__(64) k_adj_items(AdjFinishArgs a) {
+  const int lane = threadIdx.x;
+  const bool nodes = (int)blockIdx.x < a.n_node_items;
+  const AdjItem it = nodes ? a.node_items[blockIdx.x] : a.direct_items[blockIdx.x - a.n_node_items];
+  const gc_task& tk = a.tasks[it.t0];
+  const int e0 = it.base - (nodes ? a.noff : a.joff)[it.t0];  // the item's first visit of the task
+  const int W = nodes ? kAdjNodeWaves : kAdjDirectWaves;
+  if (lane <= W) (nodes ? a.ncuts : a.dcuts)[it.cuts + lane] = e0 + (int)((int64_t)it.count * lane / W);
+  uint16_t* place = nodes ? a.vpos : a.dpos;
+  for (int u = lane; u < it.count; u += 64) place[it.base + u] = (uint16_t)u;
+  if (nodes) {
+    for (int u = lane; u < it.count; u += 64) a.nsrc[it.base + u] = gld(a.nodes + tk.n_first + e0 + u);
+    return;
+  }
+  int at = -e0;  // of a range's first source among the item's
+  for (int r = 0; r < tk.j_nranges && at < it.count; ++r) {
+    const int2 g = gld(a.ranges + tk.j_first + r);
+    const int u1 = it.count - at < g.y ? it.count - at : g.y;
+    for (int u = (at < 0 ? -at : 0) + lane; u < u1; u += 64) a.dsrc_id[it.base + at + u] = g.x + u;
+    at += g.y;
+  }
+}
+
+// The direct records' positions in the union, and the ids of the sorted ones.
+__global__ void __launch_bounds__(256) k_adj_keys(AdjFinishArgs a) {
+  for (int64_t r = blockIdx.x * (int64_t)256 + threadIdx.x; r < a.n_direct; r += (int64_t)gridDim.x * 256) {
+    const int id = gld(a.dsrc_id + r);
+    int lo = 0, hi = a.n_union;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (gld(a.U + mid) < id) lo = mid + 1;
+      else hi = mid;
+    }
+    a.dsrc_packed[r] = lo;
+    a.dkey[r] = gld(a.dsrc_id + gld(a.dvis + r));
+  }
+}
+
 constexpr int kMaxTypes = 8;
 constexpr int kLJTile = 128;
 
@@ -1136,6 +1176,14 @@ hipError_t adj_both(const GravAdjArgs& a, int n_cu, hipStream_t s) {
 hipError_t launch_grav_adjoint(bool packed, int order, const GravAdjArgs& a, int n_cu, hipStream_t s) {
   if (order == 2) return packed ? adj_both<true, 2>(a, n_cu, s) : adj_both<false, 2>(a, n_cu, s);
   return packed ? adj_both<true, 1>(a, n_cu, s) : adj_both<false, 1>(a, n_cu, s);
+}
+
+hipError_t launch_adj_finish(const AdjFinishArgs& a, hipStream_t s) {
+  if (a.one_task && a.n_node_items + a.n_direct_items > 0)
+    hipLaunchKernelGGL(k_adj_items, dim3(a.n_node_items + a.n_direct_items), dim3(64), 0, s, a);
+  if (a.n_direct > 0)
+    hipLaunchKernelGGL(k_adj_keys, dim3(a.n_direct < 4096 * 256 ? (a.n_direct + 255) / 256 : 4096), dim3(256), 0, s, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_record_sums(int order, const float4* vdir, const int32_t* dvis, const int32_t* dkey, int32_t n_direct,

@@ -324,16 +324,16 @@ constexpr int kAdjMaxTasks = 16;  // tasks per item
 // Records of one node are summed in chunks of at most this many (one wavefront per chunk), so that a
 // node found in nearly every task's list adds no long serial tail.
 constexpr int kVisitChunk = 256;
-// The adjoint's indices, built on the host (adj_index.hip): one block of bytes to upload, with the places of
-// its arrays.
+// The adjoint's indices (adj_index.hip): the places of their arrays in one device buffer, and the first `bytes` of
+// it, built on the host, to upload.  What follows from those and the batch's lists is written on the device
+// (launch_adj_finish): the direct records' packed positions and sorted keys, and, with an item a task, places, cuts
+// and keys as well.
 struct AdjIndexInput {
   const gc_task* tasks;
   int32_t n_tasks;
   const int32_t* ranges;   // pairs
   const int32_t* nodes;
   int32_t n_nodes, n_ids, n_cu;
-  const int32_t* U;        // the union, ascending
-  int32_t n_union;
 };
 struct AdjIndex {
   enum { kNodeItems, kDirectItems, kNodeFirst, kNodePlace, kDirectPlace, kNodeCuts, kDirectCuts, kNodeKey, kDirectKey,
@@ -342,13 +342,34 @@ struct AdjIndex {
     void operator()(char* p) const { std::free(p); }
   };
   std::unique_ptr<char[], Free> blob;
-  size_t bytes = 0, at[kArrays] = {0};
+  size_t bytes = 0, room = 0, at[kArrays] = {0};
+  bool one_task = false;  // an item is one task, or a stretch of one, and a record one visit
   int32_t node_items = 0, direct_items = 0, max_nodes = 0, max_direct = 0, chunks = 0;
   int64_t node_recs = 0, direct_recs = 0, bad_entry = -1;
 };
 enum { kAdjIndexOk = 0, kAdjIndexBadNode, kAdjIndexTooLarge, kAdjIndexNoMemory };
 // May throw std::bad_alloc.  kAdjIndexBadNode: list entry bad_entry names a node >= n_nodes.
 int adj_index_build(const AdjIndexInput& in, AdjIndex* out);
+struct AdjFinishArgs {
+  const gc_task* tasks;
+  const int2* ranges;      // by id
+  const int32_t* nodes;
+  bool one_task;
+  const AdjItem* node_items;
+  const AdjItem* direct_items;
+  int32_t n_node_items, n_direct_items;
+  const int32_t* noff;     // per task: its first node visit,
+  const int32_t* joff;     // and its first direct visit
+  uint16_t *vpos, *dpos;
+  int32_t *ncuts, *dcuts, *nsrc, *dsrc_id;
+  const int32_t* U;        // the union, ascending
+  int32_t n_union;
+  const int32_t* dvis;     // direct records by source id
+  int32_t n_direct;
+  int32_t* dsrc_packed;    // per direct record: its source's position in U
+  int32_t* dkey;           // the sorted records' ids
+};
+hipError_t launch_adj_finish(const AdjFinishArgs& a, hipStream_t s);
 // order 1: monopole nodes (one float4 per node record); order 2: quadrupole nodes (three)
 hipError_t launch_grav_adjoint(bool packed, int order, const GravAdjArgs& a, int n_cu, hipStream_t s);
 // The gradient records, gathered through the indices built on the host: node records

@@ -1086,8 +1086,7 @@ static gc_status build_adj_index(gc_batch b, int32_t n_nodes, hipStream_t s) {
   gc_ctx c = b->ctx;
   gc_status hs = need_host_lists(b, s);
   if (hs != GC_OK) return hs;
-  AdjIndexInput in{b->tasks.data(), b->nt, b->ranges.data(), b->nodes.data(), n_nodes, b->n_ids, c->n_cu, b->hU.data(),
-                   (int32_t)b->hU.size()};
+  AdjIndexInput in{b->tasks.data(), b->nt, b->ranges.data(), b->nodes.data(), n_nodes, b->n_ids, c->n_cu};
   AdjIndex x;
   int r;
   try {
@@ -1105,9 +1104,35 @@ static gc_status build_adj_index(gc_batch b, int32_t n_nodes, hipStream_t s) {
   b->adj_nodes = -1;
   const int64_t vdir = 3 * x.node_recs, part = vdir + x.direct_recs;
   hipError_t e = b->arec.ensure(sizeof(float4) * (size_t)(part + 3 * (int64_t)std::max(x.chunks, 1)));
-  if (e == hipSuccess) e = b->aidx.ensure(x.bytes);
+  if (e == hipSuccess) e = b->aidx.ensure(x.room);
   if (e != hipSuccess) return set_err(c, GC_E_NOMEM, "gc_backward: gradient records");
   GC_HIP(c, hipMemcpyAsync(b->aidx.p, x.blob.get(), x.bytes, hipMemcpyHostToDevice, s));
+  auto at = [&](int which) { return b->aidx.as<char>() + x.at[which]; };
+  auto words = [&](int which) { return reinterpret_cast<int32_t*>(at(which)); };
+  AdjFinishArgs f{};
+  f.tasks = b->d_tasks.as<gc_task>();
+  f.ranges = b->d_ranges.as<int2>();
+  f.nodes = b->d_nodes.as<int32_t>();
+  f.one_task = x.one_task;
+  f.node_items = reinterpret_cast<const AdjItem*>(at(AdjIndex::kNodeItems));
+  f.direct_items = reinterpret_cast<const AdjItem*>(at(AdjIndex::kDirectItems));
+  f.n_node_items = x.node_items;
+  f.n_direct_items = x.direct_items;
+  f.noff = words(AdjIndex::kNodeFirst);
+  f.joff = b->d_joff.as<int32_t>();
+  f.vpos = reinterpret_cast<uint16_t*>(at(AdjIndex::kNodePlace));
+  f.dpos = reinterpret_cast<uint16_t*>(at(AdjIndex::kDirectPlace));
+  f.ncuts = words(AdjIndex::kNodeCuts);
+  f.dcuts = words(AdjIndex::kDirectCuts);
+  f.nsrc = words(AdjIndex::kNodeKey);
+  f.dsrc_id = words(AdjIndex::kDirectKey);
+  f.U = b->d_U.as<int32_t>();
+  f.n_union = b->u;
+  f.dvis = words(AdjIndex::kDirectSorted);
+  f.n_direct = (int32_t)x.direct_recs;
+  f.dsrc_packed = words(AdjIndex::kDirectPacked);
+  f.dkey = words(AdjIndex::kDirectSortedKey);
+  GC_HIP(c, launch_adj_finish(f, s));
   GC_HIP(c, hipStreamSynchronize(s));  // the host block goes out of scope
   b->adj = std::move(x);
   b->adj.blob.reset();

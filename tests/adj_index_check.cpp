@@ -27,11 +27,10 @@ namespace {
 
 struct Input {
   std::vector<gc_task> tasks;
-  std::vector<int32_t> ranges, nodes, U;
+  std::vector<int32_t> ranges, nodes;
   int32_t n_nodes = 0, n_ids = 0;
   AdjIndexInput in(int n_cu) const {
-    return AdjIndexInput{tasks.data(), (int32_t)tasks.size(), ranges.data(), nodes.data(), n_nodes, n_ids, n_cu, U.data(),
-                         (int32_t)U.size()};
+    return AdjIndexInput{tasks.data(), (int32_t)tasks.size(), ranges.data(), nodes.data(), n_nodes, n_ids, n_cu};
   }
   void add(int targets, const std::vector<int32_t>& node, const std::vector<std::pair<int32_t, int32_t>>& direct) {
     gc_task t{};
@@ -47,16 +46,6 @@ struct Input {
       ranges.push_back(r.second);
     }
     tasks.push_back(t);
-  }
-  void close() {
-    std::vector<uint8_t> in_u((size_t)n_ids, 0);
-    for (const gc_task& t : tasks) {
-      for (int32_t i = 0; i < t.i_count; ++i) in_u[(size_t)(t.i_begin + i)] = 1;
-      for (int32_t r = 0; r < t.j_nranges; ++r)
-        for (int32_t k = 0; k < ranges[2 * (t.j_first + r) + 1]; ++k) in_u[(size_t)(ranges[2 * (t.j_first + r)] + k)] = 1;
-    }
-    for (int32_t k = 0; k < n_ids; ++k)
-      if (in_u[(size_t)k]) U.push_back(k);
   }
 };
 
@@ -84,7 +73,6 @@ Input make(int form, int seed, int n_tasks) {
     }
     x.add(upto(9), node, direct);
   }
-  x.close();
   return x;
 }
 
@@ -107,9 +95,6 @@ int check(const Input& x, const AdjIndex& a, bool direct, int form, int seed) {
   const int T = (int)x.tasks.size(), cap = direct ? kAdjMaxDirect : kAdjMaxNodes;
   const int waves = direct ? kAdjDirectWaves : kAdjNodeWaves, n_items = direct ? a.direct_items : a.node_items;
   const AdjItem* item = arr<AdjItem>(a, direct ? AdjIndex::kDirectItems : AdjIndex::kNodeItems);
-  const uint16_t* place = arr<uint16_t>(a, direct ? AdjIndex::kDirectPlace : AdjIndex::kNodePlace);
-  const int32_t* cuts = arr(a, direct ? AdjIndex::kDirectCuts : AdjIndex::kNodeCuts);
-  const int32_t* key = arr(a, direct ? AdjIndex::kDirectKey : AdjIndex::kNodeKey);
   std::vector<std::vector<int32_t>> source((size_t)T);
   std::vector<int64_t> first((size_t)T + 1, 0);
   for (int t = 0; t < T; ++t) {
@@ -121,6 +106,28 @@ int check(const Input& x, const AdjIndex& a, bool direct, int form, int seed) {
     else
       s.assign(x.nodes.begin() + k.n_first, x.nodes.begin() + k.n_first + k.n_count);
     first[(size_t)t + 1] = first[(size_t)t] + (int64_t)s.size();
+  }
+  // with an item a task, the device writes places, cuts and keys: a record is a visit, and the cuts are even
+  std::vector<uint16_t> place_;
+  std::vector<int32_t> cuts_, key_;
+  const uint16_t* place = arr<uint16_t>(a, direct ? AdjIndex::kDirectPlace : AdjIndex::kNodePlace);
+  const int32_t* cuts = arr(a, direct ? AdjIndex::kDirectCuts : AdjIndex::kNodeCuts);
+  const int32_t* key = arr(a, direct ? AdjIndex::kDirectKey : AdjIndex::kNodeKey);
+  if (a.one_task) {
+    place_.resize((size_t)first[(size_t)T]);
+    cuts_.resize((size_t)n_items * (size_t)(waves + 1));
+    for (auto& s : source) key_.insert(key_.end(), s.begin(), s.end());
+    for (int i = 0; i < n_items; ++i) {
+      const AdjItem& it = item[i];
+      const int64_t e0 = it.base - first[(size_t)it.t0];
+      CHECK(it.nt == 1 && e0 >= 0 && it.base + it.count <= first[(size_t)it.t0 + 1]);
+      CHECK((size_t)it.cuts + (size_t)waves < cuts_.size());
+      for (int w = 0; w <= waves; ++w) cuts_[(size_t)(it.cuts + w)] = (int32_t)(e0 + (int64_t)it.count * w / waves);
+      for (int u = 0; u < it.count; ++u) place_[(size_t)(it.base + u)] = (uint16_t)u;
+    }
+    place = place_.data();
+    cuts = cuts_.data();
+    key = key_.data();
   }
   std::vector<uint8_t> seen((size_t)first[(size_t)T], 0);
   std::vector<std::vector<int32_t>> found((size_t)T);

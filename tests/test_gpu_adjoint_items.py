@@ -80,6 +80,27 @@ def test_long_tasks_among_many(ctx):
     _check(ctx, w, 1)
 
 
+def test_long_tasks_among_runs(ctx):
+    # 5,300 tasks, items of five: stretches of one task's sources between runs of several (every 50th task of one target
+    # has every particle in its direct list, the others their own neighbourhood)
+    w = W.build_grav(W.uniform_cube(5300, 98), bucket=1, theta=0.9)
+    assert w.n_tasks >= 5 * 4 * 256
+    w.ranges = np.concatenate([w.ranges, [[0, w.n]]]).astype(np.int32)
+    w.j_first, w.j_nr = w.j_first.copy(), w.j_nr.copy()
+    w.j_first[::50] = w.ranges.shape[0] - 1
+    w.j_nr[::50] = 1
+    _check(ctx, w, 2)
+
+
+@pytest.mark.parametrize("tasks", [5 * 1024 - 1, 5 * 1024])
+@pytest.mark.parametrize("mode", [gc.REORG_NONE, gc.REORG_PACK])
+def test_either_side_of_the_line(ctx, tasks, mode):
+    # an item a task, whose records the device writes, and items of five tasks, whose records come from the host (256 CUs)
+    w = W.build_grav(W.plummer(tasks, 102), bucket=1, theta=0.9)
+    assert w.n_tasks == tasks
+    _check(ctx, w, 2, mode)
+
+
 @pytest.mark.parametrize("lists", ["reversed", "repeated", "no_nodes", "no_direct", "some_empty"])
 def test_lists_of_any_form(ctx, lists):
     w = W.build_grav(W.plummer(3000, 95), bucket=16, theta=0.8)
