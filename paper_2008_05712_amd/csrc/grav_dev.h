@@ -446,7 +446,9 @@ __device__ __forceinline__ void grav_task_body(const GravArgs& a, const int t, c
   const __amdgpu_buffer_rsrc_t nodes = node_rsrc(a.nodes, a.n_nodes);
   if (!have_pf) node_prefetch<ORDER>(nodes, a.node_idx, tk.n_first, tk.n_count, pf);
   ready();
-  // 64 of the task's ranges, through a raw buffer (zeros past the last); the first are loaded ahead of the node tiles
+  // 64 of the task's ranges, through a raw buffer (zeros past the last); the first are loaded ahead of the node tiles, but
+  // with two targets a lane, where there are no registers to hold them over those (they were spilled, and the bench's
+  // step moved 574 MB for 532)
   auto load_ranges = [&](int rg) {
     const int n = tk.j_nranges - rg < 64 ? tk.j_nranges - rg : 64;
     const __amdgpu_buffer_rsrc_t ranges = __builtin_amdgcn_make_buffer_rsrc(
@@ -456,7 +458,8 @@ __device__ __forceinline__ void grav_task_body(const GravArgs& a, const int t, c
     return make_int2((int)v[0], (int)v[1]);
   };
   int2 g0 = make_int2(0, 0);
-  if (!LISTS) g0 = load_ranges(0);
+  constexpr bool ahead = !LISTS && TPL == 1;
+  if (ahead) g0 = load_ranges(0);
   for (int i0 = 0; i0 < ic; i0 += 64) {
     if (i0 > 0) node_prefetch<ORDER>(nodes, a.node_idx, tk.n_first, tk.n_count, pf);
     const bool last = i0 + 64 >= ic;
@@ -578,7 +581,7 @@ __device__ __forceinline__ void grav_task_body(const GravArgs& a, const int t, c
       // W contiguous, nearly equal shares of every group's records, and each lane copies one flat
       // position at a time (flat_record)
       for (int rg = 0; rg < tk.j_nranges; rg += 64) {
-        const int2 g = rg == 0 ? g0 : load_ranges(rg);
+        const int2 g = ahead && rg == 0 ? g0 : load_ranges(rg);
         int total;
         const int o = wave_excl_scan(g.y, &total);
         total = uniform(total);
