@@ -50,7 +50,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6))) k
     const gc_task g = a.tasks[t];
     const dev::TaskDesc td{uniform(g.i_begin), uniform(g.i_count), uniform(g.j_first), uniform(g.j_nranges),
                            uniform(g.n_first), uniform(g.n_count), uniform(a.ibeg ? a.ibeg[t] : g.i_begin)};
-    dev::NodePrefetch<ORDER> pf;
+    dev::NodePrefetch<ORDER, LISTS> pf;
     grav_task<ORDER, LISTS, TPL, POT>(a, t, td, smem, pf, false, [] {}, [](int) {});
   }
 }
@@ -120,7 +120,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6)))
   const StepItem it = cload(&cst(items)[blockIdx.x]);
   const GravArgs ga = cload(&cst(rounds)[it.kind]);
   const dev::TaskDesc td{it.i_begin, it.i_count, it.j_first, it.j_nranges, it.n_first, it.n_count, it.idx};
-  dev::NodePrefetch<ORDER> pf;
+  dev::NodePrefetch<ORDER, false> pf;
   grav_task<ORDER, false, TPL>(ga, 0, td, smem, pf, false, [] {}, [](int) {});
 }
 

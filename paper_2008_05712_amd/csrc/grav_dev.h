@@ -324,11 +324,13 @@ __device__ __forceinline__ void store_node(float4* L, int e, const NodeRegs<ORDE
 
 // Nodes per lane of a node tile: a monopole node is one record and its term 13 instructions, so a tile of 64
 // would cost more to stage than to sum.  Two per lane: three, the room of a quadrupole tile, take registers that
-// the potential's form does not have (535 k particles in 16 systems: 398 us with two, 420 with three).
-template <int ORDER>
-constexpr int kNodesPerLane = ORDER == 1 ? 2 : 1;
-template <int ORDER>
-constexpr int kNodesPerTile = kNodesPerLane<ORDER> * kNodeTile;
+// the potential's form does not have (535 k particles in 16 systems: 398 us with two, 420 with three).  With address
+// lists one: the second takes them from seven wavefronts a SIMD to six (Plummer 131,072, two targets a lane:
+// 91.6 us with one, 101.3 with two; 60,000 uniform in buckets of 16: 52.8 and 60.2).
+template <int ORDER, bool LISTS>
+constexpr int kNodesPerLane = ORDER == 1 && !LISTS ? 2 : 1;
+template <int ORDER, bool LISTS>
+constexpr int kNodesPerTile = kNodesPerLane<ORDER, LISTS> * kNodeTile;
 
 // This wavefront's entries w, w + W, ... of a task's node list (nw of them) as a raw buffer: entry e + lane is
 // word (e + lane) W, and a load past the last one returns zero with no branch.  A longer list than kOneBuffer entries
@@ -341,41 +343,41 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t idx_rsrc(const int* first, int
 
 // The first node tile of a task for the calling wavefront (nodes w, w + W, ... of the task's list): the
 // records in registers, entries lane, lane + 64, ..., and the indices of the nodes a whole tile on.
-template <int ORDER>
+template <int ORDER, bool LISTS>
 struct NodePrefetch {
-  NodeRegs<ORDER> cur[kNodesPerLane<ORDER>];
-  int idx_next[kNodesPerLane<ORDER>];
+  NodeRegs<ORDER> cur[kNodesPerLane<ORDER, LISTS>];
+  int idx_next[kNodesPerLane<ORDER, LISTS>];
 };
 
 // Entries e + 64 q + lane of the wavefront's nodes (nw of them): their indices, and the records of given indices.
-template <int ORDER>
+template <int ORDER, bool LISTS>
 __device__ __forceinline__ void load_idx(__amdgpu_buffer_rsrc_t il, int e, int W, int* __restrict__ idx) {
   // (the whole offset in the vector part, which alone the bounds check is certain to cover)
   const int v = ((int)(threadIdx.x & 63) + e) * W * 4;
 #pragma unroll
-  for (int q = 0; q < kNodesPerLane<ORDER>; ++q)
+  for (int q = 0; q < kNodesPerLane<ORDER, LISTS>; ++q)
     idx[q] = (int)__builtin_amdgcn_raw_buffer_load_b32(il, v + 64 * q * W * 4, 0, 0);
 }
-template <int ORDER>
+template <int ORDER, bool LISTS>
 __device__ __forceinline__ void load_nodes(__amdgpu_buffer_rsrc_t nodes, int e, int nw,
                                            const int* __restrict__ idx, NodeRegs<ORDER>* __restrict__ r) {
   const int lane = threadIdx.x & 63;
 #pragma unroll
-  for (int q = 0; q < kNodesPerLane<ORDER>; ++q)
+  for (int q = 0; q < kNodesPerLane<ORDER, LISTS>; ++q)
     r[q] = load_node<ORDER>(nodes, lane < nw - e - 64 * q ? idx[q] : -1);
 }
 
-template <int ORDER>
+template <int ORDER, bool LISTS>
 __device__ __forceinline__ void node_prefetch(__amdgpu_buffer_rsrc_t nodes, const int* __restrict__ node_idx,
-                                              int n_first, int n_count, NodePrefetch<ORDER>& pf) {
+                                              int n_first, int n_count, NodePrefetch<ORDER, LISTS>& pf) {
   const int wid = uniform(threadIdx.x >> 6);
   const int W = blockDim.x >> 6;
   const int nw = n_count > wid ? (int)((uint32_t)(n_count - wid + W - 1) / (uint32_t)W) : 0;
   const __amdgpu_buffer_rsrc_t il = idx_rsrc(node_idx + n_first + wid, nw < kOneBuffer ? nw : kOneBuffer, W);
-  int idx[kNodesPerLane<ORDER>];
-  load_idx<ORDER>(il, 0, W, idx);
-  load_idx<ORDER>(il, kNodesPerTile<ORDER>, W, pf.idx_next);
-  load_nodes<ORDER>(nodes, 0, nw, idx, pf.cur);
+  int idx[kNodesPerLane<ORDER, LISTS>];
+  load_idx<ORDER, LISTS>(il, 0, W, idx);
+  load_idx<ORDER, LISTS>(il, kNodesPerTile<ORDER, LISTS>, W, pf.idx_next);
+  load_nodes<ORDER, LISTS>(nodes, 0, nw, idx, pf.cur);
 }
 
 // Records of LDS per wavefront for a direct tile of `tile` records: the larger of a direct tile and
@@ -424,7 +426,7 @@ struct TaskDesc {
 // task's direct ranges has contributed m r^-1 at r = eps, which is taken out again).
 template <int ORDER, bool LISTS, int TPL, bool POT = false, class Ready, class Next>
 __device__ __forceinline__ void grav_task_body(const GravArgs& a, const int t, const TaskDesc& tk,
-                                          float4* __restrict__ smem, NodePrefetch<ORDER>& pf, bool have_pf,
+                                          float4* __restrict__ smem, NodePrefetch<ORDER, LISTS>& pf, bool have_pf,
                                           Ready&& ready, Next&& next) {
   static_assert(TPL == 1 || TPL == 2, "one or two targets per lane");
   static_assert(!POT || (TPL == 1 && !LISTS), "the potential runs one target per lane in position space");
@@ -444,7 +446,7 @@ __device__ __forceinline__ void grav_task_body(const GravArgs& a, const int t, c
   // this wave's nodes; the first tile does not depend on the records, so its loads go out first
   const int nw = tk.n_count > wid ? (int)((uint32_t)(tk.n_count - wid + W - 1) / (uint32_t)W) : 0;
   const __amdgpu_buffer_rsrc_t nodes = node_rsrc(a.nodes, a.n_nodes);
-  if (!have_pf) node_prefetch<ORDER>(nodes, a.node_idx, tk.n_first, tk.n_count, pf);
+  if (!have_pf) node_prefetch<ORDER, LISTS>(nodes, a.node_idx, tk.n_first, tk.n_count, pf);
   ready();
   // 64 of the task's ranges, through a raw buffer (zeros past the last); the first are loaded ahead of the node tiles, but
   // with two targets a lane, where there are no registers to hold them over those (they were spilled, and the bench's
@@ -461,7 +463,7 @@ __device__ __forceinline__ void grav_task_body(const GravArgs& a, const int t, c
   constexpr bool ahead = !LISTS && TPL == 1;
   if (ahead) g0 = load_ranges(0);
   for (int i0 = 0; i0 < ic; i0 += 64) {
-    if (i0 > 0) node_prefetch<ORDER>(nodes, a.node_idx, tk.n_first, tk.n_count, pf);
+    if (i0 > 0) node_prefetch<ORDER, LISTS>(nodes, a.node_idx, tk.n_first, tk.n_count, pf);
     const bool last = i0 + 64 >= ic;
     const int icc = ic - i0 < 64 ? ic - i0 : 64;
     constexpr bool two = TPL == 2;
@@ -480,7 +482,7 @@ __device__ __forceinline__ void grav_task_body(const GravArgs& a, const int t, c
       const int c = (int)(((uint32_t)room * mS) >> 16);
       return S * (c < kFlushTerms ? c : kFlushTerms);
     };
-    const int NT = fit(kNodesPerTile<ORDER>);  // nodes per node tile
+    const int NT = fit(kNodesPerTile<ORDER, LISTS>);  // nodes per node tile
     const int DT = fit(tile);                  // records per direct tile
     const int ib = il + h < icc ? il + h : il;  // two: second target (a copy of the first if absent)
     float3 A = make_float3(0.f, 0.f, 0.f), B = A;
@@ -534,23 +536,23 @@ __device__ __forceinline__ void grav_task_body(const GravArgs& a, const int t, c
       const int n = nw - n0 < kOneBuffer ? (int)(nw - n0) : kOneBuffer;
       const __amdgpu_buffer_rsrc_t mine = idx_rsrc(a.node_idx + tk.n_first + wid + n0 * W, n, W);
       if (n0 > 0) {
-        load_idx<ORDER>(mine, 0, W, pf.idx_next);
-        load_nodes<ORDER>(nodes, 0, n, pf.idx_next, pf.cur);
-        load_idx<ORDER>(mine, kNodesPerTile<ORDER>, W, pf.idx_next);
+        load_idx<ORDER, LISTS>(mine, 0, W, pf.idx_next);
+        load_nodes<ORDER, LISTS>(nodes, 0, n, pf.idx_next, pf.cur);
+        load_idx<ORDER, LISTS>(mine, kNodesPerTile<ORDER, LISTS>, W, pf.idx_next);
       }
       // the prefetched indices are those of a whole tile on; with NT below that the next tile starts at
       // node NT.  A tile is read up to S * C <= NT records, and past its last node it holds zero records
       // (entries past NT are the next tile's first ones, not read in this one)
-      if (NT < kNodesPerTile<ORDER>) load_idx<ORDER>(mine, NT, W, pf.idx_next);
+      if (NT < kNodesPerTile<ORDER, LISTS>) load_idx<ORDER, LISTS>(mine, NT, W, pf.idx_next);
       for (int nb = 0; nb < n; nb += NT) {
         const int cnt = n - nb < NT ? n - nb : NT;
         const int C = uniform((int)((uint32_t)(cnt + S - 1) / (uint32_t)S));
 #pragma unroll
-        for (int q = 0; q < kNodesPerLane<ORDER>; ++q) store_node<ORDER>(L, 64 * q + lane, pf.cur[q], a.eps2);
+        for (int q = 0; q < kNodesPerLane<ORDER, LISTS>; ++q) store_node<ORDER>(L, 64 * q + lane, pf.cur[q], a.eps2);
         // prefetch the next tile's records and the indices of the one after
         if (nb + NT < n) {
-          load_nodes<ORDER>(nodes, nb + NT, n, pf.idx_next, pf.cur);
-          load_idx<ORDER>(mine, nb + 2 * NT, W, pf.idx_next);
+          load_nodes<ORDER, LISTS>(nodes, nb + NT, n, pf.idx_next, pf.cur);
+          load_idx<ORDER, LISTS>(mine, nb + 2 * NT, W, pf.idx_next);
         }
         wave_sync();
         // monopole: a = -M d / r^3 with d = x_i - com, the same as a pair term from a source at com
@@ -681,7 +683,7 @@ __device__ __forceinline__ void grav_task_body(const GravArgs& a, const int t, c
 // lanes (two_fills_more), so that each form's registers are live only in its own branch.
 template <int ORDER, bool LISTS, int TPL, bool POT = false, class Ready, class Next>
 __device__ __forceinline__ void grav_task(const GravArgs& a, const int t, const TaskDesc& tk,
-                                          float4* __restrict__ smem, NodePrefetch<ORDER>& pf, bool have_pf,
+                                          float4* __restrict__ smem, NodePrefetch<ORDER, LISTS>& pf, bool have_pf,
                                           Ready&& ready, Next&& next) {
   if constexpr (TPL == 3) {
     if (two_fills_more(tk.i_count))

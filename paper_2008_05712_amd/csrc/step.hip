@@ -149,7 +149,7 @@ __global__ void __launch_bounds__(dev::kRThreads) __attribute__((amdgpu_waves_pe
   int ready = -1;  // this block has seen the data parts of rounds <= ready complete
   // a force item followed by a force item loads the next one's first node tile and (thread 0) its
   // round's data-part count while it finishes
-  dev::NodePrefetch<ORDER> pf;
+  dev::NodePrefetch<ORDER, false> pf;
   bool have_pf = false;
   int poll_k = -1;
   uint64_t poll_v = 0;
@@ -210,7 +210,7 @@ __global__ void __launch_bounds__(dev::kRThreads) __attribute__((amdgpu_waves_pe
         if ((kind2 & 3) != kItemForce) return;
         const int k2 = kind2 >> 2;
         const __attribute__((address_space(4))) StepRound& R2 = cst(s.rounds)[k2];
-        dev::node_prefetch<ORDER>(dev::node_rsrc(R2.grav.nodes, R2.grav.n_nodes), R2.grav.node_idx, uni(s_item[cb ^ 1].n_first),
+        dev::node_prefetch<ORDER, false>(dev::node_rsrc(R2.grav.nodes, R2.grav.n_nodes), R2.grav.node_idx, uni(s_item[cb ^ 1].n_first),
                                   uni(s_item[cb ^ 1].n_count), pf);
         pf_next = true;
         if (tid == 0 && k2 > ready) {

@@ -72,3 +72,41 @@ def test_tile_edges(ctx, order, bucket, shape):
             assert np.all(acc[:, 3].view(np.int32) == 0)
     b.destroy()
     rig.close()
+
+
+@pytest.mark.parametrize("order", [1, 2])
+@pytest.mark.parametrize("mode", [gc.REORG_INDIRECT, gc.REORG_SORTED])
+@pytest.mark.parametrize("shape", [dict(), dict(targets_per_lane=2, waves_per_block=1),
+                                   dict(schedule=1, targets_per_lane=3, waves_per_block=8)])
+def test_tile_edges_of_address_lists(ctx, order, mode, shape):
+    # (with address lists a monopole node tile holds 64 nodes, else 128)
+    for bucket in (3, 24, 90):
+        print(f"[gpu] grav tile edges, address lists, order={order} bucket={bucket} mode={mode} {shape}", flush=True)
+        w, bt = _edges(bucket, 302)
+        rig = GravRig(ctx, w)
+        b = rig.batch(bt)
+        acc = rig.run(b, mode, order=order, **shape)
+        err = rel_l2_per_task(acc, O.grav_workload(w, order=order, tasks=bt), bt)
+        assert err.max() <= TOL, (err.max(), int(err.argmax()))
+        b.destroy()
+        rig.close()
+
+
+@pytest.mark.parametrize("order", [1, 2])
+def test_node_list_longer_than_a_raw_buffer(ctx, order):
+    # one wavefront's list of 2^25 + 1,000 entries is read in two stretches (its own nodes over and over)
+    w = W.build_grav(W.plummer(300, 303), bucket=4, theta=1.0)
+    t = int(np.argmax(w.n_count))
+    own = w.node_idx[w.n_first[t]:w.n_first[t] + w.n_count[t]]
+    L = (1 << 25) + 1000
+    one = lambda v: np.array([v], np.int32)  # noqa: E731
+    bt = dict(i_begin=one(w.i_begin[t]), i_count=one(w.i_count[t]), j_first=one(0), j_nr=one(0),
+              ranges=np.zeros((0, 2), np.int32), n_first=one(0), n_count=one(L), node_idx=np.resize(own, L).astype(np.int32))
+    print(f"[gpu] grav node list of {L} entries order={order}", flush=True)
+    rig = GravRig(ctx, w)
+    b = rig.batch(bt)
+    acc = rig.run(b, gc.REORG_NONE, order=order, waves_per_block=1)
+    err = rel_l2_per_task(acc, O.grav_workload(w, order=order, tasks=bt), bt)
+    assert err.max() <= TOL, err.max()
+    b.destroy()
+    rig.close()
