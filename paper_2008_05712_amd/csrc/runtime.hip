@@ -2559,14 +2559,6 @@ extern "C" gc_status gc_autotune(gc_batch b, const gc_force_params* base, const 
 
 // ===================================================================== interaction lists (tree walk)
 
-namespace {
-struct ScopedBuf {  // device scratch of one call, freed on every return path
-  DevBuf d;
-  explicit ScopedBuf(gc_ctx c) { d.h = &c->hooks; }
-  ~ScopedBuf() { d.release(); }
-};
-}  // namespace
-
 // The walk proper, on scratch the caller provides: skip (int32 [n_nodes]), tot (5 int64: the two
 // totals, the invalid-bucket count, and the group walk's overflow count and order flag), and either the
 // group walk's buffers (grp) or optionally each bucket's room of the count pass (sn / sr, nullptr:
