@@ -198,9 +198,9 @@ __global__ void __launch_bounds__(256) k_lj(LJArgs a) {
 // decision accepts is dropped; the decision itself is unchanged.
 //
 // What bounds it: the issue of vector instructions.  A cell of the million-atom box (12 atoms, 321 sources of which 240 survive)
-// takes 51 evaluations of 19.5 and some 360 more: 45 a step (the entry of each source is counted from
+// takes 51 evaluations of 19.5 and some 340 more: 42 a step (the entry of each source is counted from
 // marks, 13, where a search took 30), 60 for the box, 60 for the entries.  Before, 1,800 in all and 249 us a pass; now
-// 1,360 and 175 us.  Taking the cutoff decision for all sources first and the force for the hits
+// 1,340 and 175 us.  Taking the cutoff decision for all sources first and the force for the hits
 // alone needs fewer instructions, but the hits' serial LDS reads made it 242 us.
 constexpr int kGHold = 64;               // staged sources a wavefront holds without evaluating them (128: fewer
                                          // padded slices, but 24 wavefronts a CU instead of 32: 193 against 188 us)
