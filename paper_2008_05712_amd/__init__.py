@@ -369,9 +369,10 @@ def tree_walk(ctx: "Context", node_range, node_com, node_side, rec, bucket_node,
     nb = int(bucket_node.numel())
     # The walk writes on `stream`, so the outputs come from that stream's memory: what the current one gave back may
     # still be in use there.  They may be used on both.
-    handle, current = _stream(stream), torch.cuda.current_stream(dev)
-    on = current
-    if (handle or 0) != current.cuda_stream:
+    current = torch.cuda.current_stream(dev)
+    handle, on = current.cuda_stream, current
+    if stream is not None and (_stream(stream) or 0) != handle:
+        handle = _stream(stream)
         on = torch.cuda.ExternalStream(handle, device=dev) if handle else torch.cuda.default_stream(dev)
 
     def empty(size):
